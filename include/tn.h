@@ -250,7 +250,8 @@ int tn_contract_backward(tn_plan_t plan, const void* const* leaves,
  * n_ops receives the number of ops of one batch's program and, for i <
  * min(n_ops, cap), op_ms[i] the summed duration of op i over all batches,
  * op_kind[i] its kernel (0 row, 1 split-K, 2 split-K reduce, 3 GEMM,
- * 4 FP64 accumulation, 5 permute, 6 batch counter, 7 BF16x3 operand split),
+ * 4 FP64 accumulation, 5 permute, 6 batch counter, 7 BF16x3 operand split,
+ * 8 a launch of groups of small contractions, op_node then one of their nodes),
  * op_node[i] its tree node
  * (-1 if none), op_flops[i] / op_bytes[i] its algorithmic complex FLOPs and
  * bytes per in-flight slice.  Any output array may be NULL.

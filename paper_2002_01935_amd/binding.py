@@ -32,7 +32,7 @@ EXPORTS = [
     "tn_plan_tune_trials", "tn_contract_sliced_noalloc", "tn_batch", "tn_batch_info", "tn_batch_prepare",
     "tn_batch_contract", "tn_batch_destroy", "tn_plan_backward_kernels",
 ]
-OP_KINDS = {0: "row", 1: "splitk", 2: "reduce", 3: "gemm", 4: "accum", 5: "permute", 6: "counter", 7: "split"}
+OP_KINDS = {0: "row", 1: "splitk", 2: "reduce", 3: "gemm", 4: "accum", 5: "permute", 6: "counter", 7: "split", 8: "tiny"}
 
 
 class TNError(RuntimeError):

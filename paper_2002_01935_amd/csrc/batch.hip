@@ -35,6 +35,7 @@ namespace tn {
 #define TN_UNIFORM(x) __builtin_amdgcn_readfirstlane(x)
 
 #include "rowops.h"
+#include "tiny_kernel.h"
 
 constexpr int kTinyBits = 16;       // bit-list capacity of a tiny contraction
 constexpr int kTinyWorkBits = 16;   // log2 (outputs x summed values) of the largest one
@@ -48,14 +49,14 @@ constexpr int kBranches = 4;
 // (opX = complex conjugate when conj_x), or C[o] (+)= opA(A[o]) without B.
 // Output bit j sits at position oa[j] / ob[j] / oc[j] of A / B / C (-1:
 // absent from that operand), summed bit j at ka[j] / kb[j].
-struct TinyOp {
+struct BatchOp {
   Ref a, b, c;
   int32_t n_out, n_k;
   int32_t has_b, conj_a, conj_b, accumulate;
   int8_t oa[kTinyBits], ob[kTinyBits], oc[kTinyBits];
   int8_t ka[kTinyBits], kb[kTinyBits];
 };
-static_assert(offsetof(TinyOp, oa) % 4 == 0 && sizeof(TinyOp) % 8 == 0, "TinyOp layout");
+static_assert(offsetof(BatchOp, oa) % 4 == 0 && sizeof(BatchOp) % 8 == 0, "BatchOp layout");
 
 __device__ __forceinline__ int tpos(CMEM const int8_t* list, int i) {
   const uint32_t w = reinterpret_cast<CMEM const uint32_t*>(list)[i >> 2];
@@ -72,18 +73,6 @@ __device__ __forceinline__ uint32_t tdeposit(uint32_t v, CMEM const int8_t* list
   return off;
 }
 
-// Copy of a uniform read-only struct (scalar loads, a dword at a time).
-template <typename S>
-__device__ __forceinline__ S cload(CMEM const S* p) {
-  static_assert(sizeof(S) % 4 == 0, "dword copy");
-  S out;
-  CMEM const uint32_t* w = reinterpret_cast<CMEM const uint32_t*>(p);
-  uint32_t* o = reinterpret_cast<uint32_t*>(&out);
-#pragma unroll
-  for (int i = 0; i < (int)(sizeof(S) / 4); i++) o[i] = w[i];
-  return out;
-}
-
 template <typename V>
 __device__ __forceinline__ V conj_if(V v, int c) {
   if (c) v.y = -v.y;
@@ -96,7 +85,7 @@ __device__ __forceinline__ V conj_if(V v, int c) {
 // values walked with per-carry offset steps, and the 2^g partial sums are
 // added in a fixed tree order (results do not depend on scheduling).
 template <typename T>
-__global__ __launch_bounds__(kTinyThreads) void tiny_kernel(CMEM const Ctx* ctxs, CMEM const TinyOp* ops,
+__global__ __launch_bounds__(kTinyThreads) void tiny_kernel(CMEM const Ctx* ctxs, CMEM const BatchOp* ops,
                                                             CMEM const int32_t* seg) {
   using V = typename C2<T>::t;
   const int net = blockIdx.x;
@@ -107,7 +96,7 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_kernel(CMEM const Ctx* ctxs
   __shared__ uint32_t kd[2][kTinyBits];
   __shared__ V red[kTinyThreads];
   for (int i = begin; i < end; i++) {
-    CMEM const TinyOp* op = ops + i;
+    CMEM const BatchOp* op = ops + i;
     const int n_out = op->n_out, n_k = op->n_k, has_b = op->has_b;
     const int ca = op->conj_a, cb = op->conj_b, accum = op->accumulate;
     const int g = n_out < 8 ? min(8 - n_out, n_k) : 0;
@@ -184,8 +173,23 @@ __global__ __launch_bounds__(kTinyThreads) void tiny_kernel(CMEM const Ctx* ctxs
   }
 }
 
+// The small-contraction launches that begin each network's program, all in one
+// launch: workgroup b runs group entry[b].group of the blob at entry[b].blob
+// bytes from the workspace base, for network entry[b].net.
+struct BatchGroup {
+  uint32_t net, group;
+  uint64_t blob;
+};
+template <typename T>
+__global__ __launch_bounds__(512) void tiny_batch_kernel(uint64_t base, CMEM const Ctx* ctxs, CMEM const BatchGroup* entries) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];
+  const BatchGroup e = cload(entries + blockIdx.x);
+  const Ctx ctx = cload(ctxs + e.net);
+  tiny_group<T>(ctx, base + e.blob, (int)e.group, 0, 0, smem);
+}
+
 // Whether op runs inside the interpreter, and its descriptor if so.
-static bool as_tiny(const Op& op, int prec, TinyOp& t) {
+static bool as_tiny(const Op& op, int prec, BatchOp& t) {
   std::memset(&t, 0, sizeof t);
   for (int j = 0; j < kTinyBits; j++) t.oa[j] = t.ob[j] = t.oc[j] = t.ka[j] = t.kb[j] = -1;
   if (op.kind == OpKind::Row) {
@@ -246,9 +250,15 @@ struct tn_batch_s {
   std::vector<int32_t> n_leaves;             // per network
   std::vector<uint64_t> region_off;          // per network: its plan workspace inside the batch workspace
   std::vector<Ctx> ctx_rel;                  // per network, ws relative to the batch workspace base
-  std::vector<TinyOp> tiny;                  // ordered by level, then network
+  std::vector<BatchOp> tiny;                  // ordered by level, then network
   std::vector<int32_t> seg;                  // [level][network] -> begin, end in `tiny`
   std::vector<std::vector<std::vector<Op>>> big;   // [level][network] -> ops launched after the segment
+  // leading small-contraction groups of all networks: blobs, workgroup table
+  std::vector<char> blobs;
+  std::vector<BatchGroup> groups;
+  int64_t n_grouped = 0;                     // contractions in them
+  uint32_t group_threads = 64, group_lds = 0;
+  uint64_t blob_off = 0, group_off = 0;
   uint64_t ctx_off = 0, ops_off = 0, seg_off = 0, ptr_off = 0, ws_bytes = 0;
   int ptr_stride = 0;                        // pointer-table slots per network
   int64_t n_launches = 0;
@@ -289,7 +299,7 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
   b->prec = prec;
   b->n_nets = n_plans;
   // per network: the mode-0 program cut into (segment, following large ops) levels
-  std::vector<std::vector<std::vector<TinyOp>>> segs(n_plans);
+  std::vector<std::vector<std::vector<BatchOp>>> segs(n_plans);
   std::vector<std::vector<std::vector<Op>>> bigs(n_plans);
   for (int j = 0; j < n_plans; j++) {
     tn_plan_s* p = plans[j];
@@ -297,9 +307,20 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
     std::vector<Op> prog = forward_program(p, 0);
     segs[j].emplace_back();
     bigs[j].emplace_back();
+    bool leading = true;
     for (const Op& op : prog) {
       if (op.kind == OpKind::Counter || op.kind == OpKind::Fill) continue;
-      TinyOp t;
+      if (op.kind == OpKind::Tiny && leading) {
+        for (uint32_t g = 0; g < op.tiny->n_groups; g++) b->groups.push_back({(uint32_t)j, g, b->blobs.size()});
+        b->blobs.insert(b->blobs.end(), op.tiny->blob.begin(), op.tiny->blob.end());
+        b->blobs.resize((b->blobs.size() + 63) / 64 * 64, 0);
+        b->group_threads = std::max(b->group_threads, op.tiny->threads);
+        b->group_lds = std::max(b->group_lds, op.tiny->lds_bytes);
+        b->n_grouped += (int64_t)op.tiny->nodes.size();
+        continue;
+      }
+      leading = false;
+      BatchOp t;
       if (as_tiny(op, prec, t)) {
         if (!bigs[j].back().empty()) {   // a tiny op after large ones starts the next level
           segs[j].emplace_back();
@@ -330,9 +351,12 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
   auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
   b->ctx_off = 0;
   b->ops_off = up(b->ctx_off + sizeof(Ctx) * (uint64_t)N);
-  b->seg_off = up(b->ops_off + sizeof(TinyOp) * (uint64_t)std::max<size_t>(b->tiny.size(), 1));
+  b->seg_off = up(b->ops_off + sizeof(BatchOp) * (uint64_t)std::max<size_t>(b->tiny.size(), 1));
   b->ptr_off = up(b->seg_off + sizeof(int32_t) * (uint64_t)b->seg.size());
-  uint64_t off = up(b->ptr_off + 8 * (uint64_t)b->ptr_stride * N);
+  b->blob_off = up(b->ptr_off + 8 * (uint64_t)b->ptr_stride * N);
+  b->group_off = up(b->blob_off + b->blobs.size());
+  for (BatchGroup& g : b->groups) g.blob += b->blob_off;
+  uint64_t off = up(b->group_off + sizeof(BatchGroup) * (uint64_t)b->groups.size());
   for (int j = 0; j < N; j++) {
     tn_plan_s* p = plans[j];
     b->region_off.push_back(off);
@@ -342,7 +366,7 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
     off = up(off + p->workspace_bytes);
   }
   b->ws_bytes = off;
-  int64_t launches = 0;
+  int64_t launches = b->groups.empty() ? 0 : 1;
   for (int l = 0; l < L; l++) {
     launches += 1;
     for (int j = 0; j < N; j++) launches += (int64_t)b->big[l][j].size();
@@ -358,7 +382,7 @@ extern "C" int tn_batch_info(tn_batch_t b, uint64_t* workspace_bytes, int32_t* n
   std::lock_guard<std::mutex> lk(b->mu);
   if (workspace_bytes) *workspace_bytes = b->ws_bytes;
   if (n_levels) *n_levels = b->n_levels;
-  if (n_tiny) *n_tiny = (int64_t)b->tiny.size();
+  if (n_tiny) *n_tiny = b->n_grouped + (int64_t)b->tiny.size();
   if (n_launches) *n_launches = b->n_launches;
   return TN_OK;
 }
@@ -382,8 +406,12 @@ extern "C" int tn_batch_prepare(tn_batch_t b, void* workspace, uint64_t workspac
   for (int j = 0; j < b->n_nets; j++) ctxs.push_back(batch_ctx(b, j, base));
   BATCH_TRY(hipMemcpyAsync(w + b->ctx_off, ctxs.data(), sizeof(Ctx) * ctxs.size(), hipMemcpyHostToDevice, s));
   if (!b->tiny.empty())
-    BATCH_TRY(hipMemcpyAsync(w + b->ops_off, b->tiny.data(), sizeof(TinyOp) * b->tiny.size(), hipMemcpyHostToDevice, s));
+    BATCH_TRY(hipMemcpyAsync(w + b->ops_off, b->tiny.data(), sizeof(BatchOp) * b->tiny.size(), hipMemcpyHostToDevice, s));
   BATCH_TRY(hipMemcpyAsync(w + b->seg_off, b->seg.data(), sizeof(int32_t) * b->seg.size(), hipMemcpyHostToDevice, s));
+  if (!b->groups.empty()) {
+    BATCH_TRY(hipMemcpyAsync(w + b->blob_off, b->blobs.data(), b->blobs.size(), hipMemcpyHostToDevice, s));
+    BATCH_TRY(hipMemcpyAsync(w + b->group_off, b->groups.data(), sizeof(BatchGroup) * b->groups.size(), hipMemcpyHostToDevice, s));
+  }
   // each network's batch counter and slice-id list: 0 (one slice, id 0)
   for (int j = 0; j < b->n_nets; j++) {
     const Ctx c = ctxs[(size_t)j];
@@ -415,9 +443,17 @@ extern "C" int tn_batch_prepare(tn_batch_t b, void* workspace, uint64_t workspac
   }
   if (e == hipSuccess) e = hipStreamBeginCapture(cs[0], hipStreamCaptureModeThreadLocal);
   const int N = b->n_nets;
+  if (e == hipSuccess && !b->groups.empty()) {
+    CMEM const Ctx* dctx = reinterpret_cast<CMEM const Ctx*>(base + b->ctx_off);
+    CMEM const BatchGroup* dgrp = reinterpret_cast<CMEM const BatchGroup*>(base + b->group_off);
+    const dim3 grid((unsigned)b->groups.size()), block(b->group_threads);
+    if (b->prec == TN_C128) hipLaunchKernelGGL(tiny_batch_kernel<double>, grid, block, b->group_lds, cs[0], base, dctx, dgrp);
+    else hipLaunchKernelGGL(tiny_batch_kernel<float>, grid, block, b->group_lds, cs[0], base, dctx, dgrp);
+    e = hipGetLastError();
+  }
   for (int l = 0; l < b->n_levels && e == hipSuccess; l++) {
     CMEM const Ctx* dctx = reinterpret_cast<CMEM const Ctx*>(base + b->ctx_off);
-    CMEM const TinyOp* dops = reinterpret_cast<CMEM const TinyOp*>(base + b->ops_off);
+    CMEM const BatchOp* dops = reinterpret_cast<CMEM const BatchOp*>(base + b->ops_off);
     CMEM const int32_t* dseg = reinterpret_cast<CMEM const int32_t*>(base + b->seg_off + sizeof(int32_t) * 2 * (uint64_t)l * N);
     if (b->prec == TN_C128) hipLaunchKernelGGL(tiny_kernel<double>, dim3(N), dim3(kTinyThreads), 0, cs[0], dctx, dops, dseg);
     else hipLaunchKernelGGL(tiny_kernel<float>, dim3(N), dim3(kTinyThreads), 0, cs[0], dctx, dops, dseg);

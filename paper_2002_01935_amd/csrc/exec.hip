@@ -111,6 +111,7 @@ extern "C" int tn_plan(int32_t n_leaves, const int32_t* rank, const int64_t* lea
     return set_err(TN_E_INVALID, "unknown precision");
   }
   p->elem_bytes = p->prec == TN_C128 ? 16 : 8;
+  p->group_small = true;
   std::string err;
   int rc = build_plan(p, err);
   if (rc) {
@@ -229,6 +230,7 @@ static const char* op_kernel_name(const tn_plan_s* p, const Op& op, int* tile) {
     case OpKind::Permute: return "permute_kernel";
     case OpKind::Counter: return "counter_kernel";
     case OpKind::Split: return "split_kernel";
+    case OpKind::Tiny: return "tiny_tree_kernel";
     default: return "";
   }
 }
@@ -239,8 +241,12 @@ extern "C" int tn_plan_node_kernel(tn_plan_t p, int32_t k, int32_t* tile, char* 
   if (k < 0 || k >= (int32_t)p->nodes.size()) return set_err(TN_E_INVALID, "node out of range");
   const int node = p->n_leaves + k;
   const Op* main = nullptr;
-  for (const Op& op : p->fwd)
-    if (op.node == node && (op.kind == OpKind::Gemm || op.kind == OpKind::Row)) { main = &op; break; }
+  for (const Op& op : p->fwd) {
+    const bool holds = op.kind == OpKind::Tiny
+                           ? std::find(op.tiny->nodes.begin(), op.tiny->nodes.end(), node) != op.tiny->nodes.end()
+                           : op.node == node && (op.kind == OpKind::Gemm || op.kind == OpKind::Row);
+    if (holds) { main = &op; break; }
+  }
   if (!main) return set_err(TN_E_INVALID, "node has no contraction op");
   int t = -1;
   const char* nm = op_kernel_name(p, *main, &t);
@@ -260,14 +266,15 @@ extern "C" int tn_plan_backward_kernels(tn_plan_t p, int32_t n_wrt, const int32_
   if (rc) return rc;
   int32_t i = 0;
   for (const Op& op : p->bwd) {
-    if (op.kind != OpKind::Gemm && op.kind != OpKind::Row) continue;
-    if (names && name_cap > 0 && i < cap) {
+    if (op.kind != OpKind::Gemm && op.kind != OpKind::Row && op.kind != OpKind::Tiny) continue;
+    const int32_t held = op.kind == OpKind::Tiny ? (int32_t)op.tiny->nodes.size() : 1;   // contractions of the launch
+    for (int32_t j = 0; j < held; j++, i++) {
+      if (!names || name_cap <= 0 || i >= cap) continue;
       int t = -1;
       char* dst = names + (size_t)i * (size_t)name_cap;
       std::strncpy(dst, op_kernel_name(p, op, &t), (size_t)name_cap - 1);
       dst[name_cap - 1] = 0;
     }
-    i++;
   }
   *n = i;
   return TN_OK;
@@ -317,6 +324,7 @@ hipError_t tn::launch_op(int prec, const Ctx& ctx, const Op& op, hipStream_t s) 
     case OpKind::Fill: return hipSuccess;
     case OpKind::Counter: return launch_counter(ctx, 1, 1, s);
     case OpKind::Split: return launch_split(ctx, op.split, s);
+    case OpKind::Tiny: return launch_tiny(ctx, *op.tiny, f64, s);
   }
   return hipErrorInvalidValue;
 }
@@ -357,6 +365,20 @@ std::vector<Op> tn::forward_program(const tn_plan_s* p, int mode) {
   // (the root layout is already the output order and the storage type).
   if (mode == 0 && n > 1) {
     const int root_node = 2 * n - 2;
+    for (Op& o : prog) {
+      if (o.kind != OpKind::Tiny || o.tiny->root_op < 0) continue;
+      auto L = std::make_shared<TinyLaunch>(*o.tiny);
+      TinyOp t;
+      std::memcpy(&t, L->blob.data() + L->root_op, sizeof t);
+      t.dst_kind = 2;
+      t.dst = (uint32_t)p->slot_out;
+      std::memcpy(L->blob.data() + L->root_op, &t, sizeof t);
+      o.tiny = L;
+      Op c;
+      c.kind = OpKind::Counter;
+      prog.push_back(c);
+      return prog;
+    }
     bool direct = true;
     for (const Op& o : prog) {
       if (o.node != root_node) continue;
@@ -614,6 +636,7 @@ static int op_kind_code(const Op& op) {
     case OpKind::Permute: return 5;
     case OpKind::Counter: return 6;
     case OpKind::Split: return 7;
+    case OpKind::Tiny: return 8;
     default: return -1;
   }
 }

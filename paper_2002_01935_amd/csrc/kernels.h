@@ -15,6 +15,8 @@ hipError_t launch_permute(const Ctx& ctx, const PermuteOp& op, bool f64, hipStre
 hipError_t launch_accum(const Ctx& ctx, const AccumOp& op, bool f64, hipStream_t s);
 hipError_t launch_counter(const Ctx& ctx, int64_t value, int add, hipStream_t s);
 hipError_t launch_fill(uint64_t base, uint64_t bytes, hipStream_t s);
+struct TinyLaunch;
+hipError_t launch_tiny(const Ctx& ctx, const TinyLaunch& L, bool f64, hipStream_t s);
 hipError_t launch_split(const Ctx& ctx, const SplitOp& op, hipStream_t s);
 // Workgroups (of 4 wavefronts) along x of a persistent launch of `kernel`
 // that needs `waves` wavefronts per grid row, with gy grid rows: about

@@ -354,7 +354,7 @@ constexpr int kMaxSplitSumBits = 13;
 // writes 8 (A) or 16 (B) bytes per element.
 constexpr int kMinPresplitBits = 28;
 
-static void push(Prog& prog, Op op);
+static void push(Prog& prog, const Op& op);
 
 // The split of one operand of a BF16x3 GEMM (see SplitOp): rows = the free
 // bits (positions `fpos`), then the batch bits (`hpos`); summed bits `kpos`.
@@ -416,8 +416,6 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
   std::sort(K.begin(), K.end(), [&](int x, int y) { return A.lay.pos_of(x) < A.lay.pos_of(y); });
 
   Op op;
-  std::memset(&op.row, 0, sizeof op.row);
-  std::memset(&op.gemm, 0, sizeof op.gemm);
   op.node = node;
   int64_t out_elems = int64_t(1) << cb.size();
   double fl = 8.0 * std::exp2(h + m + n + k);
@@ -524,7 +522,7 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
   return op;
 }
 
-static void push(Prog& prog, Op op) {
+static void push(Prog& prog, const Op& op) {
   int idx = (int)prog.ops.size();
   if (op.kind == OpKind::Row) {
     prog.touch(op.row.a, idx); prog.touch(op.row.b, idx); prog.touch(op.row.c, idx);
@@ -658,6 +656,8 @@ static int classes(tn_plan_s* p, std::string& err) {
   return TN_OK;
 }
 
+#include "tiny_group.h"
+
 // First-fit arena allocation from buffer lifetimes.
 static uint64_t allocate(Prog& prog) {
   struct Ev { int t; int kind; int buf; };   // kind 0 = alloc, 1 = free
@@ -690,6 +690,15 @@ static uint64_t allocate(Prog& prog) {
     peak = std::max<uint64_t>(peak, (uint64_t)(cur + sz));
   }
   auto fix = [&](Ref& r) { if (r.kind == 1) r.off = prog.bufs[(size_t)r.off].off; };
+  auto fix_tiny = [&](Op& op) {
+    auto L = std::make_shared<TinyLaunch>(*op.tiny);
+    for (auto* list : {&L->reads, &L->writes})
+      for (auto& x : *list) {
+        const uint32_t at = (uint32_t)(prog.bufs[(size_t)x.second].off / align);   // TinyLoad::src / TinyOp::dst
+        std::memcpy(L->blob.data() + x.first, &at, 4);
+      }
+    op.tiny = L;
+  };
   for (Op& op : prog.ops) {
     switch (op.kind) {
       case OpKind::Row:
@@ -704,10 +713,54 @@ static uint64_t allocate(Prog& prog) {
       case OpKind::Accum: fix(op.accum.src); fix(op.accum.dst); break;
       case OpKind::Permute: fix(op.perm.src); fix(op.perm.dst); break;
       case OpKind::Split: fix(op.split.src); fix(op.split.dst); break;
+      case OpKind::Tiny: fix_tiny(op); break;
       default: break;
     }
   }
   return peak;
+}
+
+// Arena layout of a program, its small contractions grouped if `accept`s the
+// arena that results (a group's external values live from the group's launch
+// on, so it can be larger than without).
+template <typename F>
+static uint64_t allocate_grouped(const tn_plan_s* p, Prog& prog, int root_buf, F&& accept) {
+  if (!p->group_small) {
+    if (root_buf >= 0) prog.extend(root_buf, (int)prog.ops.size());   // read by the tail
+    return allocate(prog);
+  }
+  Prog grouped = group_small(p, prog, root_buf);
+  if (root_buf >= 0) {
+    prog.extend(root_buf, (int)prog.ops.size());
+    grouped.extend(root_buf, (int)grouped.ops.size());
+  }
+  const uint64_t plain = allocate(prog), bytes = allocate(grouped);
+  if (!accept(plain, bytes)) return plain;
+  prog = std::move(grouped);
+  return bytes;
+}
+
+// In-flight slices of a plan whose arena takes `arena` bytes.
+static int inflight(const tn_plan_s* p, uint64_t arena) {
+  int nb = p->opt.max_inflight_slices;
+  if (nb <= 0) {
+    nb = 1;
+    if (p->opt.workspace_cap > 0) nb = (int)std::max<uint64_t>(1, p->opt.workspace_cap / std::max<uint64_t>(arena, 1));
+  }
+  nb = (int)std::min<int64_t>(nb, std::max<int64_t>(1, p->d_sliced));
+  return std::min(nb, 65535);
+}
+
+// Whether a grouped program may take an arena of `grouped` bytes in place of
+// `plain`: all in-flight arenas together grow by at most 1/64 or 4 MiB, about
+// as many slices are in flight, and a workspace that fits the library's static
+// scratch (64 MiB, slice-id tables of up to 34 MiB included) still does.
+static bool arena_ok(const tn_plan_s* p, uint64_t plain, uint64_t grouped) {
+  const int na = inflight(p, std::max<uint64_t>(plain, 256)), nb = inflight(p, std::max<uint64_t>(grouped, 256));
+  if (4 * nb < 3 * na) return false;
+  const uint64_t a = plain * na, b = grouped * nb, scratch = uint64_t(64) << 20, tables = uint64_t(34) << 20;
+  if (a <= scratch && b > a && b + tables > scratch) return false;
+  return b <= a + std::max<uint64_t>(a / 64, uint64_t(4) << 20);
 }
 
 static Operand node_operand(const tn_plan_s* p, int v, const std::vector<int>& bufs) {
@@ -746,6 +799,7 @@ int build_plan(tn_plan_s* p, std::string& err) {
   // forward program: one contraction per internal node in tree order; the
   // root's value stays in the arena for the mode-specific tail
   Prog prog;
+  prog.ops.reserve((size_t)n + n / 4);
   std::vector<int> bufs(nn, -1);
   for (int v = n; v < nn; v++) bufs[v] = prog.new_buf(node_bytes(p, v));
   for (int k = 0; k < n - 1; k++) {
@@ -760,19 +814,12 @@ int build_plan(tn_plan_s* p, std::string& err) {
     ni.k_split_bits = op.row.k_split_bits;
     push(prog, op);
   }
-  if (nn - 1 >= n) prog.extend(bufs[nn - 1], (int)prog.ops.size());   // root read by the tail
-  p->arena_bytes = std::max<uint64_t>(allocate(prog), 256);
-  p->fwd = prog.ops;
+  p->arena_bytes = std::max<uint64_t>(allocate_grouped(p, prog, n > 1 ? bufs[nn - 1] : -1,
+                                                      [&](uint64_t x, uint64_t y) { return arena_ok(p, x, y); }), 256);
+  p->fwd = std::move(prog.ops);
   p->root_off = n > 1 ? prog.bufs[(size_t)bufs[nn - 1]].off : -1;
   // in-flight slices
-  int nb = p->opt.max_inflight_slices;
-  if (nb <= 0) {
-    nb = 1;
-    if (p->opt.workspace_cap > 0)
-      nb = (int)std::max<uint64_t>(1, p->opt.workspace_cap / std::max<uint64_t>(p->arena_bytes, 1));
-  }
-  nb = (int)std::min<int64_t>(nb, std::max<int64_t>(1, p->d_sliced));
-  nb = std::min(nb, 65535);
+  const int nb = inflight(p, p->arena_bytes);
   p->n_batch = nb;
   int64_t max_ids = std::min<int64_t>(std::max<int64_t>(p->d_sliced, nb), int64_t(1) << 22);
   max_ids = (max_ids + nb - 1) / nb * nb;
@@ -827,6 +874,7 @@ int build_backward(tn_plan_s* p, const std::vector<int32_t>& wrt, std::string& e
     if ((int)(i % stride) == stride - 1 || i + 1 == large.size()) ckpt[large[i]] = 1;
 
   Prog prog;
+  prog.ops.reserve((size_t)4 * n);
   std::vector<int> vbuf(nn, -1);   // current buffer holding the node value
   double flops = 0;
   auto emit_forward = [&](int v) {
@@ -923,8 +971,10 @@ int build_backward(tn_plan_s* p, const std::vector<int32_t>& wrt, std::string& e
     release(v);
     gbuf[v] = -1;
   }
-  p->bwd_arena_bytes = std::max<uint64_t>(allocate(prog), 256);
-  p->bwd = prog.ops;
+  p->bwd_arena_bytes = std::max<uint64_t>(allocate_grouped(p, prog, -1, [&](uint64_t x, uint64_t y) {
+    return y <= x + std::max<uint64_t>(x / 64, uint64_t(4) << 20);
+  }), 256);
+  p->bwd = std::move(prog.ops);
   p->bwd_wrt = wrt;
   p->bwd_flops_per_slice = flops;
   uint64_t ws;

@@ -4,18 +4,32 @@
 #include <array>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
 
 #include "../../include/tn.h"
+#include "tiny.h"
 #include "tn_internal.h"
 
 namespace tn {
 
-enum class OpKind { Row, RowReduce, Gemm, Accum, Permute, Fill, Counter, Split };
+enum class OpKind { Row, RowReduce, Gemm, Accum, Permute, Fill, Counter, Split, Tiny };
 
 enum KernelClass { kRow = 0, kSplitK = 1, kGemm = 2, kGemmSplitK = 3 };
+
+// One launch of the small-contraction kernel: its blob, and what the host
+// still needs to know about it.
+struct TinyLaunch {
+  std::vector<char> blob;
+  uint32_t n_groups = 0, threads = 0, lds_bytes = 0;
+  std::vector<int> nodes;             // tree node of every contraction
+  // where the blob names arena buffers: byte offset of the uint32 field,
+  // buffer id (replaced by offset / 256 once the arena is laid out)
+  std::vector<std::pair<uint32_t, int>> reads, writes;
+  int64_t root_op = -1;               // byte offset of the TinyOp that writes the root value
+};
 
 struct Op {
   Op() { std::memset(&row, 0, sizeof row); std::memset(&gemm, 0, sizeof gemm);
@@ -28,6 +42,7 @@ struct Op {
   AccumOp accum;
   PermuteOp perm;
   SplitOp split;
+  std::shared_ptr<const TinyLaunch> tiny;
   int64_t fill_off = 0, fill_bytes = 0;   // Fill: arena range to zero
   int32_t fill_slot = -1;                 // Fill: pointer-table slot (bytes = fill_bytes) instead
   double flops = 0, bytes = 0;            // algorithmic, per slice
@@ -68,6 +83,10 @@ struct tn_plan_s {
   tn_options opt{};
   int prec = TN_C64_4M;
   int elem_bytes = 8;
+
+  // collect small contractions into groups (tiny_group.h); off for callers
+  // that run the program op by op on the host
+  bool group_small = false;
 
   // bit expansion
   std::vector<int> bit_base, bit_count;   // per index

@@ -92,6 +92,18 @@ __device__ __forceinline__ uint64_t deposit_opt(uint64_t v, const int8_t* pos, i
   return off;
 }
 
+// Copy of a uniform read-only struct (scalar loads, a dword at a time).
+template <typename S>
+__device__ __forceinline__ S cload(CMEM const S* p) {
+  static_assert(sizeof(S) % 4 == 0, "dword copy");
+  S out;
+  CMEM const uint32_t* w = reinterpret_cast<CMEM const uint32_t*>(p);
+  uint32_t* o = reinterpret_cast<uint32_t*>(&out);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(S) / 4); i++) o[i] = w[i];
+  return out;
+}
+
 // The batch counter, the slice-id list and the pointer table are read at
 // uniform addresses and do not change while a kernel runs: reading them
 // through the constant address space (CMEM) makes these scalar loads instead
