@@ -49,7 +49,7 @@ PEAK = {"c64_4m": 157.3, "c64_3m": 157.3, "c64_bf16x3": 2500.0, "c128": 78.6}
 # vector-ALU complex128 path 1; 3M three real products (6C); BF16x3 three
 # BF16 products of the 4M embedding (24C)
 EXECUTED = {"c64_4m": 1.0, "c64_3m": 0.75, "c64_bf16x3": 3.0, "c128": 1.0}
-KERNEL = {"c64_4m": "gemm_mfma_4m", "c64_3m": "gemm_mfma_3m", "c64_bf16x3": "gemm_mfma_bf16x3", "c128": "gemm_valu"}
+KERNEL = {"c64_4m": "gemm_mfma_4m", "c64_3m": "gemm_mfma_3m", "c64_bf16x3": "gemm_mfma_bf16x3", "c128": "gemm_mfma_f64"}
 WORKLOADS = {
     "cfg5": "6x9 grid circuit (54 qubits), 12 cycles, fSim(pi/2,pi/6) + sqrtX/Y/W, 6 open qubits "
             "(64 amplitudes), sliced to W_s=30, seeded slice ids",

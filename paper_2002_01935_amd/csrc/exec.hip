@@ -47,6 +47,9 @@ extern "C" const char* tn_last_error(void) { return g_err.c_str(); }
 
 int tn::set_error(int code, const std::string& msg) { return set_err(code, msg); }
 
+// Device memory of tn_contract_sliced_noalloc (`scratch` below), per GPU.
+constexpr uint64_t kStaticScratchBytes = uint64_t(64) << 20;
+
 using PlanLock = std::lock_guard<std::mutex>;
 
 // Wait for the last launch of a cached graph, then free it.
@@ -117,6 +120,18 @@ extern "C" int tn_plan(int32_t n_leaves, const int32_t* rank, const int64_t* lea
   if (rc) {
     delete p;
     return set_err(rc, err);
+  }
+  // splitting complex128 GEMMs must not push a plan out of the static scratch
+  if (p->prec == TN_C128 && p->workspace_bytes > kStaticScratchBytes && p->workspace_bytes <= 4 * kStaticScratchBytes) {
+    tn_plan_s* q = new tn_plan_s();
+    q->n_leaves = p->n_leaves; q->n_idx = p->n_idx; q->n_out = p->n_out; q->n_sliced = p->n_sliced;
+    q->rank = p->rank; q->leaf_idx = p->leaf_idx; q->idx_dim = p->idx_dim; q->out_idx = p->out_idx; q->sliced = p->sliced;
+    q->left = p->left; q->right = p->right;
+    q->opt = p->opt; q->prec = p->prec; q->elem_bytes = p->elem_bytes;
+    q->group_small = true;
+    q->split_f64 = false;
+    if (build_plan(q, err) == 0 && q->workspace_bytes <= kStaticScratchBytes) std::swap(p, q);
+    delete q;
   }
   assign_tiles(p, p->fwd);
   *plan = p;
@@ -591,7 +606,6 @@ extern "C" int tn_contract_sliced(tn_plan_t p, const void* const* leaves, int64_
 // `scratch` names a host-side stand-in, so host code never passes it to a
 // kernel or a copy; it uses the device address hipGetSymbolAddress returns
 // for the current device, looked up once per device.
-constexpr uint64_t kStaticScratchBytes = uint64_t(64) << 20;
 constexpr int kMaxDevices = 64;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
 static std::mutex g_scratch_mu;

@@ -22,7 +22,8 @@
 //                  [[Br Bi] [-Bi Br]] (2K x 2N), so one v_mfma_f32_32x32x2f32
 //                  with k = (re, im) is one complex multiply-add of a 32 x 16
 //                  complex tile: 4 real products (4M), FP32 accumulation.
-//   gemm_valu      tiled vector-ALU complex GEMM, used for complex128.
+//   gemm_mfma_f64  the same embedding on FP64 matrix cores (complex128).
+//   gemm_valu      tiled vector-ALU complex GEMM, the FP32 reference variant.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -1435,10 +1436,158 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(Ctx ctx, SplitReduceO
   st(C, acc);
 }
 
+// ------------------------------------------------------------------ FP64 matrix-core GEMM
+
+typedef double doublex4 __attribute__((ext_vector_type(4)));
+
+// complex128: the 4M embedding on v_mfma_f64_16x16x4_f64.  Its four real k are
+// (re, im) of two complex k and its 16 real columns 8 complex ones, so executed
+// = algorithmic FLOPs.  Lane l supplies A[row l % 16][real k l / 16] and the
+// matching entry of [[Br Bi] [-Bi Br]]: part p ^ q of its complex column, for
+// column parity p = l & 1 and k parity q = (l / 16) & 1, times a sign that is
+// fixed per lane (the conjugations included).  LDS keeps the complex values
+// interleaved, BK complex k per row and stage, rows padded by 16 bytes.  One
+// op takes 64 cycles and a wave issues FM * FN per 2 complex k for FM + FN
+// 8-byte LDS reads, so the matrix cores are the bound (78.6 TFLOP/s) as soon as
+// a stage's loads are covered: the next stage's are in registers while this one
+// is multiplied, and eight k per stage make that long enough for a load from
+// HBM (58.8 -> 63.6 TFLOP/s at 2^12 x 2^12 x 2^12 against four k; matrix cores
+// 81 % busy).  Against the vector-ALU kernel before: 2^12 x 2^12 x 2^12 13.2 ->
+// 8.64 ms, 2^10 x 2^13 x 2^10 1.72 -> 1.17 ms, 2^7 x 2^9 x 2^11 (split) 248 ->
+// 71 us per call.
+template <int BM, int BN, int BK, int WGM, int WGN>
+__global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2))) void gemm_mfma_f64(Ctx ctx, GemmOp op) {
+  constexpr int RK = __builtin_ctz(BK), LDR = 2 * BK + 2;
+  constexpr int NT = 64 * WGM * WGN;
+  constexpr int WM = BM / WGM, WN = BN / WGN;
+  constexpr int FM = WM / 16, FN = WN / 8;
+  constexpr int LA = BM * BK / NT, LB = BN * BK / NT;
+  constexpr int RM = __builtin_ctz(BM), RN = __builtin_ctz(BN);
+  static_assert(FM >= 1 && FN >= 1 && LA >= 1 && LB >= 1, "tile too small");
+  __shared__ __attribute__((aligned(16))) double lds[2][(BM + BN) * LDR];
+  static_assert(sizeof(lds) >= (BM + BN) * sizeof(uint64_t), "lds too small for epilogue tables");
+  GemmSetup g;
+  if (!gemm_setup(ctx, op, RM, RN, RK, g)) return;
+  GMEM const double2* A = reinterpret_cast<GMEM const double2*>(resolve(ctx, op.a, g.z, g.sid, 16)) + g.ka +
+                          deposit_runs(g.h, op.run_a_h) + deposit_runs(g.tile_m << g.tm, op.run_a_m);
+  GMEM const double2* B = reinterpret_cast<GMEM const double2*>(resolve(ctx, op.b, g.z, g.sid, 16)) + g.kb +
+                          deposit_runs(g.h, op.run_b_h) + deposit_runs(g.tile_n << g.tn, op.run_b_n);
+  const int tid = threadIdx.x;
+  uint32_t a_off[LA], b_off[LB];
+  int16_t a_dst[LA], b_dst[LB];
+  {
+    TileMap ma, mb;
+    make_tilemap(ma, op.a_m, g.tm, op.a_k, g.tk, RM);
+    make_tilemap(mb, op.b_n, g.tn, op.b_k, g.tk, RN);
+    tile_slots<LA, NT>(ma, tid, a_off, a_dst);
+    tile_slots<LB, NT>(mb, tid, b_off, b_dst);
+  }
+  for (int i = tid; i < 2 * (BM + BN) * LDR; i += NT) (&lds[0][0])[i] = 0.0;
+  __shared__ uint64_t kdel[2][kMaxBits];
+  for (int t = tid; t < op.n_k - g.tk; t += NT) {
+    const uint64_t c = (uint64_t(1) << t) - 1;
+    kdel[0][t] = step_delta(c, op.a_k, g.tk);
+    kdel[1][t] = step_delta(c, op.b_k, g.tk);
+  }
+  __syncthreads();
+
+  const uint64_t nsteps = uint64_t(1) << (op.n_k - g.tk);
+  double2 ra[LA], rb[LB];
+  uint64_t ka = 0, kb = 0, kstep = 0;
+  auto gload = [&]() {
+#pragma unroll
+    for (int i = 0; i < LA; i++) ra[i] = ld(A + ka + a_off[i]);
+#pragma unroll
+    for (int i = 0; i < LB; i++) rb[i] = ld(B + kb + b_off[i]);
+    if (kstep + 1 < nsteps) {
+      const int t = __builtin_ctzll(~kstep);
+      ka += kdel[0][t];
+      kb += kdel[1][t];
+    }
+    kstep++;
+  };
+  typedef double d2 __attribute__((ext_vector_type(2)));
+  auto put = [&](int buf, int row, int k, const double2& v) {
+    d2 w;
+    w[0] = v.x;
+    w[1] = v.y;
+    *reinterpret_cast<d2*>(&lds[buf][row * LDR + 2 * k]) = w;
+  };
+  auto sstore = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < LA; i++)
+      if (a_dst[i] >= 0) put(buf, a_dst[i] & (BM - 1), a_dst[i] >> RM, ra[i]);
+#pragma unroll
+    for (int i = 0; i < LB; i++)
+      if (b_dst[i] >= 0) put(buf, BM + (b_dst[i] & (BN - 1)), b_dst[i] >> RN, rb[i]);
+  };
+
+  const int wave = tid >> 6, lane = tid & 63;
+  const int wm = wave / WGN, wn = wave % WGN;
+  const int c16 = lane & 15, kq = lane >> 4;
+  const int p = c16 & 1, q = kq & 1;
+  const double sa = op.conj_a ? -1.0 : 1.0, sb = op.conj_b ? -1.0 : 1.0;
+  const double sign = q == 0 ? (p ? sb : 1.0) : (p ? sa : -sa * sb);
+  const int arow = (wm * WM + c16) * LDR + kq;
+  const int bcol = (BM + wn * WN + (c16 >> 1)) * LDR + (kq & 2) + (p ^ q);
+  doublex4 acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; i++)
+#pragma unroll
+    for (int j = 0; j < FN; j++) acc[i][j] = doublex4{0, 0, 0, 0};
+
+  gload();
+  sstore(0);
+  __syncthreads();
+  for (uint64_t s = 0; s < nsteps; s++) {
+    const int buf = s & 1;
+    if (s + 1 < nsteps) gload();
+#pragma unroll
+    for (int kk = 0; kk < BK / 2; kk++) {
+      double fa[FM], fb[FN];
+#pragma unroll
+      for (int i = 0; i < FM; i++) fa[i] = lds[buf][arow + i * 16 * LDR + 4 * kk];
+#pragma unroll
+      for (int j = 0; j < FN; j++) fb[j] = sign * lds[buf][bcol + j * 8 * LDR + 4 * kk];
+#pragma unroll
+      for (int j = 0; j < FN; j++)
+#pragma unroll
+        for (int i = 0; i < FM; i++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+    if (s + 1 < nsteps) sstore(buf ^ 1);
+    __syncthreads();
+  }
+  // accumulator r of lane l: row 4 r + l / 16, real column l % 16
+  GMEM double* C = reinterpret_cast<GMEM double*>(resolve(ctx, op.c, g.z, g.sid, 16));
+  const uint64_t cbase = g.cs + deposit_runs(g.h, op.run_c_h) + deposit_runs(g.tile_m << g.tm, op.run_c_m) +
+                         deposit_runs(g.tile_n << g.tn, op.run_c_n);
+  uint64_t* rowoff = reinterpret_cast<uint64_t*>(&lds[0][0]);
+  uint64_t* coloff = rowoff + BM;
+  for (int i = tid; i < BM; i += NT) rowoff[i] = deposit_runs(uint64_t(i), op.run_c_m);
+  for (int i = tid; i < BN; i += NT) coloff[i] = deposit_runs(uint64_t(i), op.run_c_n);
+  __syncthreads();
+  const int mvalid = 1 << g.tm, nvalid = 1 << g.tn;
+#pragma unroll
+  for (int j = 0; j < FN; j++) {
+    const int col = wn * WN + j * 8 + (c16 >> 1);
+    if (col >= nvalid) continue;
+    const uint64_t co = cbase + coloff[col];
+#pragma unroll
+    for (int i = 0; i < FM; i++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int row = wm * WM + i * 16 + 4 * r + kq;
+        if (row >= mvalid) continue;
+        GMEM double* dst = C + 2 * (co + rowoff[row]) + p;
+        *dst = op.accumulate ? *dst + acc[i][j][r] : acc[i][j][r];
+      }
+  }
+}
+
 // ------------------------------------------------------------------ VALU tiled GEMM
 
-// 64 x 64 complex tile, 256 threads, each thread 4 x 4 outputs; used for
-// complex128 and as the FP32 reference variant of the tile autotuner.
+// 64 x 64 complex tile, 256 threads, each thread 4 x 4 outputs: the FP32
+// reference variant of the tile autotuner.
 template <typename T>
 __global__ __launch_bounds__(256) void gemm_valu(Ctx ctx, GemmOp op) {
   using V = typename C2<T>::t;
@@ -1716,8 +1865,16 @@ bool gemm_tile_ok(const GemmOp& op, int tile, int prec) {
   return true;
 }
 
+// Block tile of a complex128 GEMM: 128 x 64 reads each operand value from LDS
+// for more products, but needs two blocks per compute unit to hide its
+// barriers; with fewer blocks than that the chip is filled by 64 x 64 tiles.
+static bool f64_wide(const GemmOp& op) {
+  const int tiles = std::max(0, op.n_m - 7) + std::max(0, op.n_n - 6) + op.n_h + std::max(0, op.k_split_bits);
+  return op.n_m >= 7 && tiles >= 9;
+}
+
 const char* gemm_kernel_name(const GemmOp& op, int prec) {
-  if (prec == TN_C128) return "gemm_valu<double>";
+  if (prec == TN_C128) return f64_wide(op) ? "gemm_mfma_f64<128,64,8,2,2>" : "gemm_mfma_f64<64,64,8,2,2>";
   if (op.tile == kValuTile) return "gemm_valu<float>";
   if (prec == TN_C64_3M) {
     switch (op.tile) {
@@ -1794,6 +1951,7 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
   if (prec == TN_C128) tile = 4;
   op.tile = tile;
   if (gemm_tile_bits(tile, &bm, &bn) || !gemm_tile_ok(op, tile, prec)) return hipErrorInvalidValue;
+  if (prec == TN_C128 && f64_wide(op)) bm = 7;
   const int tm = op.n_m < bm ? op.n_m : bm, tn = op.n_n < bn ? op.n_n : bn;
   const uint64_t tiles = uint64_t(1) << ((op.n_m - tm) + (op.n_n - tn));
   const uint64_t gy = uint64_t(ctx.n_batch) << op.n_h;
@@ -1820,7 +1978,8 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
 static hipError_t launch_gemm_kernel(const Ctx& ctx, const GemmOp& op, int prec, dim3 grid, hipStream_t s) {
   const int tile = op.tile;
   if (prec == TN_C128) {
-    hipLaunchKernelGGL(gemm_valu<double>, grid, dim3(256), 0, s, ctx, op);
+    if (f64_wide(op)) hipLaunchKernelGGL((gemm_mfma_f64<128, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op);
+    else hipLaunchKernelGGL((gemm_mfma_f64<64, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op);
     return hipGetLastError();
   }
   if (tile == 4) {

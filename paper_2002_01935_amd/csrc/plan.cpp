@@ -452,6 +452,14 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
       const int acc = std::min(std::min(k - kMaxSplitSumBits, 10), k - 1 - std::min(fa, fb));
       ks = std::max(ks, acc);
     }
+    // complex128: 64 x 64 tiles and about 7 us of FP64 matrix-core work per
+    // 2^6 summed values, so shorter parts pay; the partial buffer stays at
+    // most as large as the larger operand
+    if (p->prec == TN_C128 && p->split_f64) {
+      const int tiles64 = std::max(0, fa - 6) + std::max(0, fb - 6) + h;
+      ks = std::max(ks, std::min(std::min(k - 6, 9 - tiles64), std::max(h + fa + k, h + fb + k) - (h + fa + fb)));
+      ks = std::min(ks, 10);
+    }
     g.k_split_bits = ks > 0 ? ks : 0;
     if (ks > 0) g.part = buf_ref(prog.new_buf((int64_t)p->elem_bytes << (h + fa + fb + ks)));
     // BF16x3: split both operands once into the planes the matrix-core kernel

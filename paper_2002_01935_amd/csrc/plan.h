@@ -87,6 +87,7 @@ struct tn_plan_s {
   // collect small contractions into groups (tiny_group.h); off for callers
   // that run the program op by op on the host
   bool group_small = false;
+  bool split_f64 = true;   // complex128 GEMMs split over K for parallelism alone
 
   // bit expansion
   std::vector<int> bit_base, bit_count;   // per index
