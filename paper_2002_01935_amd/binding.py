@@ -2,13 +2,15 @@
 
 Every step of a contraction runs in libtn's HIP kernels.  PyTorch supplies
 device memory (leaves, outputs, gradients, workspace) and the stream
-(torch.cuda.current_stream()).  If libtn.so is missing this module raises on
-import: there is no fallback implementation.
+(torch.cuda.current_stream()).  If libtn.so or _leaves.so (leaf checks, host
+code) is missing this module raises on import: there is no fallback
+implementation.
 """
 
 from __future__ import annotations
 
 import ctypes
+import math
 import os
 
 import numpy as np
@@ -83,6 +85,7 @@ def _load():
 
 
 lib = _load()
+from . import _leaves  # noqa: E402
 
 
 def _check(rc):
@@ -117,7 +120,7 @@ def _on_stream(stream, make):
 
 
 def _dev_ptrs(tensors):
-    return (ctypes.c_void_p * max(1, len(tensors)))(*[t.data_ptr() for t in tensors])
+    return _leaves.pointers(tensors)
 
 
 class Plan:
@@ -135,6 +138,7 @@ class Plan:
         for r in rank:
             self.leaf_shapes.append(tuple(int(idx_dim[e]) for e in leaf_idx[off:off + r]))
             off += r
+        self._leaf_sizes = np.array([math.prod(s) for s in self.leaf_shapes], np.int64).tobytes()
         self.precision = precision
         self.prec = PRECISIONS[precision]
         keep = []
@@ -225,15 +229,16 @@ class Plan:
     # ---------------------------------------------------------------- device calls
 
     def _check_leaves(self, leaves):
-        import torch
+        """The leaves' device addresses (the pointer array the library takes)."""
         if len(leaves) != self.n_leaves:
             raise ValueError(f"expected {self.n_leaves} leaves, got {len(leaves)}")
-        for v, t in enumerate(leaves):
+        ptrs = _leaves.leaves(leaves, self.prec == TN_C128, self._leaf_sizes)
+        if isinstance(ptrs, int):
+            v, t = ptrs, leaves[ptrs]
             if not t.is_cuda or not t.is_contiguous() or t.dtype != self.storage_dtype:
                 raise ValueError(f"leaf {v} must be a contiguous {self.storage_dtype} CUDA tensor")
-            if tuple(t.shape) != self.leaf_shapes[v] and t.numel() != int(np.prod(self.leaf_shapes[v], dtype=np.int64)):
-                raise ValueError(f"leaf {v} has shape {tuple(t.shape)}, expected {self.leaf_shapes[v]}")
-        return torch
+            raise ValueError(f"leaf {v} has shape {tuple(t.shape)}, expected {self.leaf_shapes[v]}")
+        return ptrs
 
     def workspace(self, nbytes=None, stream=None):
         n = self.info()["workspace_bytes"] if nbytes is None else int(nbytes)
@@ -251,17 +256,17 @@ class Plan:
         return n.value
 
     def contract(self, leaves, out=None, workspace=None, stream=None):
-        torch = self._check_leaves(leaves)
+        ptrs = self._check_leaves(leaves)
         if out is None:
             out = _on_stream(stream, lambda: torch.empty(self.out_shape, dtype=self.storage_dtype, device="cuda"))
         if workspace is None:
             workspace = self.workspace(stream=stream)
-        _check(lib.tn_contract(self.handle, _dev_ptrs(leaves), ctypes.c_void_p(out.data_ptr()),
+        _check(lib.tn_contract(self.handle, ptrs, ctypes.c_void_p(out.data_ptr()),
                                ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream(stream)))
         return out
 
     def contract_sliced(self, leaves, slice_ids=None, out=None, workspace=None, stream=None):
-        torch = self._check_leaves(leaves)
+        ptrs = self._check_leaves(leaves)
         if out is None:
             out = _on_stream(stream, lambda: torch.empty(self.out_shape, dtype=torch.complex128, device="cuda"))
         if out.dtype != torch.complex128 or not out.is_contiguous():
@@ -273,7 +278,7 @@ class Plan:
         else:
             keep, ptr = _arr(list(slice_ids), np.int64)
             n = len(keep)
-        _check(lib.tn_contract_sliced(self.handle, _dev_ptrs(leaves), n, ptr, ctypes.c_void_p(out.data_ptr()),
+        _check(lib.tn_contract_sliced(self.handle, ptrs, n, ptr, ctypes.c_void_p(out.data_ptr()),
                                       ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream(stream)))
         return out
 
@@ -282,7 +287,7 @@ class Plan:
         no workspace, and the call allocates no device memory.  `out` is a
         caller-provided contiguous complex128 tensor; calls that overlap on
         one GPU race on the shared scratch."""
-        self._check_leaves(leaves)
+        ptrs = self._check_leaves(leaves)
         if out.dtype != torch.complex128 or not out.is_contiguous() or not out.is_cuda:
             raise ValueError("out must be a contiguous complex128 CUDA tensor")
         if slice_ids is None:
@@ -290,14 +295,14 @@ class Plan:
         else:
             keep, ptr = _arr(list(slice_ids), np.int64)
             n = len(keep)
-        _check(lib.tn_contract_sliced_noalloc(self.handle, _dev_ptrs(leaves), n, ptr, ctypes.c_void_p(out.data_ptr()),
+        _check(lib.tn_contract_sliced_noalloc(self.handle, ptrs, n, ptr, ctypes.c_void_p(out.data_ptr()),
                                               _stream(stream)))
         return out
 
     def contract_sliced_timed(self, leaves, slice_ids=None, out=None, workspace=None, stream=None):
         """tn_contract_sliced run op by op with HIP events around every launch;
         returns (out, [dict(kind, node, ms, flops, bytes) per op])."""
-        torch = self._check_leaves(leaves)
+        ptrs = self._check_leaves(leaves)
         if out is None:
             out = _on_stream(stream, lambda: torch.empty(self.out_shape, dtype=torch.complex128, device="cuda"))
         if workspace is None:
@@ -315,7 +320,7 @@ class Plan:
         by = np.zeros(cap, np.float64)
         nops = ctypes.c_int32()
         vp = lambda a: a.ctypes.data_as(ctypes.c_void_p)  # noqa: E731
-        _check(lib.tn_contract_sliced_timed(self.handle, _dev_ptrs(leaves), n, ptr, ctypes.c_void_p(out.data_ptr()),
+        _check(lib.tn_contract_sliced_timed(self.handle, ptrs, n, ptr, ctypes.c_void_p(out.data_ptr()),
                                             ctypes.c_void_p(workspace.data_ptr()), workspace.numel(), _stream(stream),
                                             cap, vp(ms), vp(kind), vp(node), vp(fl), vp(by), ctypes.byref(nops)))
         ops = [dict(kind=OP_KINDS.get(int(kind[i]), "?"), node=int(node[i]), ms=float(ms[i]), flops=float(fl[i]),
@@ -323,7 +328,7 @@ class Plan:
         return out, ops
 
     def backward(self, leaves, grad_out, wrt, grads=None, slice_ids=None, workspace=None, stream=None):
-        torch = self._check_leaves(leaves)
+        ptrs = self._check_leaves(leaves)
         wrt = [int(v) for v in wrt]
         if grads is None:
             grads = _on_stream(stream, lambda: [torch.empty(self.leaf_shapes[v], dtype=self.storage_dtype,
@@ -337,7 +342,7 @@ class Plan:
         else:
             keep, ptr = _arr(list(slice_ids), np.int64)
             n = len(keep)
-        _check(lib.tn_contract_backward(self.handle, _dev_ptrs(leaves), ctypes.c_void_p(go.data_ptr()), len(w), wp,
+        _check(lib.tn_contract_backward(self.handle, ptrs, ctypes.c_void_p(go.data_ptr()), len(w), wp,
                                         _dev_ptrs(grads), n, ptr, ctypes.c_void_p(workspace.data_ptr()),
                                         workspace.numel(), _stream(stream)))
         return grads
@@ -378,13 +383,10 @@ class Batch:
         """leaves[j] = the leaf tensors of plan j; returns the outputs."""
         if len(leaves) != len(self.plans):
             raise ValueError(f"expected leaves of {len(self.plans)} networks")
-        flat = []
-        for p, ls in zip(self.plans, leaves):
-            p._check_leaves(ls)
-            flat.extend(ls)
+        flat = b"".join(p._check_leaves(ls) for p, ls in zip(self.plans, leaves))
         if outs is None:
             outs = [_on_stream(stream, lambda p=p: torch.empty(p.out_shape, dtype=p.storage_dtype, device="cuda"))
                     for p in self.plans]
-        _check(lib.tn_batch_contract(self.handle, _dev_ptrs(flat), _dev_ptrs(outs), ctypes.c_void_p(workspace.data_ptr()),
+        _check(lib.tn_batch_contract(self.handle, flat, _dev_ptrs(outs), ctypes.c_void_p(workspace.data_ptr()),
                                      workspace.numel(), _stream(stream)))
         return outs

@@ -1,4 +1,4 @@
-"""Compile libtn.so (HIP, gfx950) in-tree.
+"""Compile libtn.so (HIP, gfx950) and the binding's _leaves.so in-tree.
 
     python -m paper_2002_01935_amd.build
 
@@ -25,7 +25,29 @@ FLAGS = [
 ]
 
 
+def build_leaves(verbose: bool = False) -> str:
+    """The binding's host extension (csrc/leaves.cpp), compiled against the
+    installed PyTorch's headers."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    out = os.path.join(HERE, "_leaves.so")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
+    for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        cmd += ["-isystem", d]
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd += [os.path.join(CSRC, "leaves.cpp"), "-o", out + ".tmp", f"-L{lib}", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(out + ".tmp", out)
+    return out
+
+
 def build(verbose: bool = False) -> str:
+    build_leaves(verbose)
     objs = []
     for src in SOURCES:
         path = os.path.join(CSRC, src)
