@@ -246,6 +246,7 @@ static const char* op_kernel_name(const tn_plan_s* p, const Op& op, int* tile) {
     case OpKind::Counter: return "counter_kernel";
     case OpKind::Split: return "split_kernel";
     case OpKind::Tiny: return "tiny_tree_kernel";
+    case OpKind::Scatter: return "scatter_kernel";
     default: return "";
   }
 }
@@ -340,6 +341,7 @@ hipError_t tn::launch_op(int prec, const Ctx& ctx, const Op& op, hipStream_t s) 
     case OpKind::Counter: return launch_counter(ctx, 1, 1, s);
     case OpKind::Split: return launch_split(ctx, op.split, s);
     case OpKind::Tiny: return launch_tiny(ctx, *op.tiny, f64, s);
+    case OpKind::Scatter: return launch_scatter(ctx, *op.tiny, f64, s);
   }
   return hipErrorInvalidValue;
 }
@@ -389,9 +391,6 @@ std::vector<Op> tn::forward_program(const tn_plan_s* p, int mode) {
       t.dst = (uint32_t)p->slot_out;
       std::memcpy(L->blob.data() + L->root_op, &t, sizeof t);
       o.tiny = L;
-      Op c;
-      c.kind = OpKind::Counter;
-      prog.push_back(c);
       return prog;
     }
     bool direct = true;
@@ -410,9 +409,6 @@ std::vector<Op> tn::forward_program(const tn_plan_s* p, int mode) {
         if (o.kind == OpKind::Row || o.kind == OpKind::RowReduce) redirect(o.row.c);
         else if (o.kind == OpKind::Gemm) redirect(o.gemm.c);
       }
-      Op c;
-      c.kind = OpKind::Counter;
-      prog.push_back(c);
       return prog;
     }
   }
@@ -437,7 +433,10 @@ std::vector<Op> tn::forward_program(const tn_plan_s* p, int mode) {
     t.accum.dst.slot = p->slot_out;
     t.accum.n = int64_t(1) << nb;
   }
+  if (t.kind == OpKind::Accum) t.accum.advance = t.accum.n <= kAccumAdvance ? 1 : 0;
   prog.push_back(t);
+  // an unsliced contraction is one batch: nothing reads the counter again
+  if (mode == 0 || (t.kind == OpKind::Accum && t.accum.advance)) return prog;
   Op c;
   c.kind = OpKind::Counter;
   prog.push_back(c);
@@ -465,11 +464,13 @@ static hipStream_t capture_stream() {
   return s;
 }
 
-// Run `prog` n_batches times on stream s: replays of the graph cached for
-// (mode, workspace) when graphs are enabled and `use_graph` is set, else
+// Run the ops that program() returns n_batches times on stream s: replays of
+// the graph cached for (mode, workspace) when graphs are enabled and
+// `use_graph` is set (the program is then built for the capture only), else
 // launch by launch.  Called with the plan's lock held.
-static int run_batches(tn_plan_s* p, int mode, const std::vector<Op>& prog, const Ctx& ctx, int64_t n_batches,
-                       hipStream_t s, bool use_graph = true) {
+template <typename F>
+static int run_batches(tn_plan_s* p, int mode, F&& program, const Ctx& ctx, int64_t n_batches, hipStream_t s,
+                       bool use_graph = true) {
   if (n_batches <= 0) return TN_OK;
   if (use_graph && graphs_enabled()) {
     auto key = std::make_pair(mode, ctx.ws);
@@ -485,7 +486,7 @@ static int run_batches(tn_plan_s* p, int mode, const std::vector<Op>& prog, cons
       hipStream_t cs = capture_stream();
       if (!cs) return set_err(TN_E_DEVICE, "could not create the capture stream");
       HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-      for (const Op& op : prog) {
+      for (const Op& op : program()) {
         hipError_t e = launch_op(p, ctx, op, cs);
         if (e != hipSuccess) {
           hipGraph_t g = nullptr;
@@ -517,6 +518,7 @@ static int run_batches(tn_plan_s* p, int mode, const std::vector<Op>& prog, cons
     HIP_TRY(hipEventRecord((hipEvent_t)it->second.done, s));
     return TN_OK;
   }
+  const std::vector<Op> prog = program();
   for (int64_t b = 0; b < n_batches; b++)
     for (const Op& op : prog) {
       hipError_t e = launch_op(p, ctx, op, s);
@@ -525,19 +527,19 @@ static int run_batches(tn_plan_s* p, int mode, const std::vector<Op>& prog, cons
   return TN_OK;
 }
 
-// Upload the pointer table and the (padded) slice ids; reset the batch counter.
+// Upload the batch counter (0), the pointer table and the (padded) slice ids:
+// one region of the workspace, one copy.
 static int upload(tn_plan_s* p, void* ws, const void* const* leaves, void* out, const void* gout,
                   void* const* grads, int n_grads, const std::vector<int64_t>& ids, hipStream_t s) {
-  std::vector<uint64_t> tab(p->n_slots, 0);
+  const size_t t0 = (size_t)(p->ptrtab_off - p->counter_off) / 8, i0 = (size_t)(p->sid_off - p->counter_off) / 8;
+  std::vector<uint64_t> head(i0 + ids.size(), 0);
+  uint64_t* tab = head.data() + t0;
   for (int v = 0; v < p->n_leaves; v++) tab[v] = reinterpret_cast<uint64_t>(leaves[v]);
   tab[p->slot_out] = reinterpret_cast<uint64_t>(out);
   tab[p->slot_gout] = reinterpret_cast<uint64_t>(gout);
   for (int i = 0; i < n_grads; i++) tab[p->slot_grad0 + i] = reinterpret_cast<uint64_t>(grads[i]);
-  char* w = static_cast<char*>(ws);
-  HIP_TRY(hipMemcpyAsync(w + p->ptrtab_off, tab.data(), tab.size() * 8, hipMemcpyHostToDevice, s));
-  HIP_TRY(hipMemcpyAsync(w + p->sid_off, ids.data(), ids.size() * 8, hipMemcpyHostToDevice, s));
-  Ctx ctx = make_ctx(p, ws, 0);
-  HIP_TRY(launch_counter(ctx, 0, 0, s));
+  for (size_t i = 0; i < ids.size(); i++) head[i0 + i] = (uint64_t)ids[i];
+  HIP_TRY(hipMemcpyAsync(static_cast<char*>(ws) + p->counter_off, head.data(), head.size() * 8, hipMemcpyHostToDevice, s));
   return TN_OK;
 }
 
@@ -585,9 +587,12 @@ static int contract_sliced_impl(tn_plan_s* p, const void* const* leaves, int64_t
   if (rc) return rc;
   const int64_t out_elems = int64_t(1) << (p->n_leaves > 1 ? p->kept_bits[2 * p->n_leaves - 2].size()
                                                            : p->layout[0].bits.size());
-  HIP_TRY(launch_fill(reinterpret_cast<uint64_t>(out_c128), (uint64_t)out_elems * 16, s));
+  // the accumulation's first batch overwrites the output (a single leaf's
+  // permute, or no batch at all, does not)
+  if (p->n_leaves == 1 || ids.empty())
+    HIP_TRY(launch_fill(reinterpret_cast<uint64_t>(out_c128), (uint64_t)out_elems * 16, s));
   Ctx ctx = make_ctx(p, workspace, p->arena_bytes);
-  return run_batches(p, 1, forward_program(p, 1), ctx, (int64_t)ids.size() / p->n_batch, s, use_graph);
+  return run_batches(p, 1, [&] { return forward_program(p, 1); }, ctx, (int64_t)ids.size() / p->n_batch, s, use_graph);
 }
 
 extern "C" int tn_contract_sliced(tn_plan_t p, const void* const* leaves, int64_t n_ids, const int64_t* slice_ids,
@@ -647,7 +652,8 @@ static int op_kind_code(const Op& op) {
     case OpKind::RowReduce: return 2;
     case OpKind::Gemm: return 3;
     case OpKind::Accum: return 4;
-    case OpKind::Permute: return 5;
+    case OpKind::Permute:
+    case OpKind::Scatter: return 5;
     case OpKind::Counter: return 6;
     case OpKind::Split: return 7;
     case OpKind::Tiny: return 8;
@@ -730,7 +736,7 @@ extern "C" int tn_contract(tn_plan_t p, const void* const* leaves, void* out, vo
   rc = upload(p, workspace, leaves, out, nullptr, nullptr, 0, ids, s);
   if (rc) return rc;
   Ctx ctx = make_ctx(p, workspace, p->arena_bytes);
-  return run_batches(p, 0, forward_program(p, 0), ctx, (int64_t)ids.size() / p->n_batch, s);
+  return run_batches(p, 0, [&] { return forward_program(p, 0); }, ctx, (int64_t)ids.size() / p->n_batch, s);
 }
 
 extern "C" int tn_contract_backward(tn_plan_t p, const void* const* leaves, const void* grad_out_c128,
@@ -756,15 +762,28 @@ extern "C" int tn_contract_backward(tn_plan_t p, const void* const* leaves, cons
   hipStream_t s = static_cast<hipStream_t>(stream);
   rc = upload(p, workspace, leaves, nullptr, grad_out_c128, grads, n_wrt, ids, s);
   if (rc) return rc;
-  for (int i = 0; i < n_wrt; i++) {
-    int v = wrt_leaf[i];
-    int64_t elems = 1;
-    for (int a = 0; a < p->rank[v]; a++) elems *= p->idx_dim[p->leaf_idx[p->leaf_off[v] + a]];
-    HIP_TRY(launch_fill(reinterpret_cast<uint64_t>(grads[i]), (uint64_t)elems * p->elem_bytes, s));
+  // zero the gradients: small ones together, large ones with a launch each
+  const Ctx zero_ctx = make_ctx(p, workspace, 0);
+  constexpr uint64_t kSmallWords = uint64_t(1) << 14;
+  for (int i = 0; i < n_wrt;) {
+    uint32_t words[kZeroArrays];
+    int n = 0;
+    uint64_t w = 0;
+    for (; i + n < n_wrt && n < kZeroArrays; n++) {
+      const int v = wrt_leaf[i + n];
+      uint64_t elems = 1;
+      for (int a = 0; a < p->rank[v]; a++) elems *= (uint64_t)p->idx_dim[p->leaf_idx[p->leaf_off[v] + a]];
+      w = elems * (uint64_t)p->elem_bytes / 8;
+      if (w > kSmallWords) break;
+      words[n] = (uint32_t)w;
+    }
+    if (n > 0) HIP_TRY(launch_zero(zero_ctx, p->slot_grad0 + i, words, n, s));
+    else HIP_TRY(launch_fill(reinterpret_cast<uint64_t>(grads[i]), w * 8, s));
+    i += std::max(n, 1);
   }
   if (n_wrt == 0) return TN_OK;
   Ctx ctx = make_ctx(p, workspace, p->bwd_arena_bytes);
-  return run_batches(p, 2, backward_program(p), ctx, (int64_t)ids.size() / p->n_batch, s);
+  return run_batches(p, 2, [&] { return backward_program(p); }, ctx, (int64_t)ids.size() / p->n_batch, s);
 }
 
 // ------------------------------------------------------------------ autotuning

@@ -17,6 +17,11 @@ hipError_t launch_counter(const Ctx& ctx, int64_t value, int add, hipStream_t s)
 hipError_t launch_fill(uint64_t base, uint64_t bytes, hipStream_t s);
 struct TinyLaunch;
 hipError_t launch_tiny(const Ctx& ctx, const TinyLaunch& L, bool f64, hipStream_t s);
+hipError_t launch_scatter(const Ctx& ctx, const TinyLaunch& L, bool f64, hipStream_t s);
+// Zeroes the arrays of pointer-table slots first_slot .. first_slot + n - 1
+// (n <= kZeroArrays), words[i] 8-byte words each.
+constexpr int kZeroArrays = 512;
+hipError_t launch_zero(const Ctx& ctx, int first_slot, const uint32_t* words, int n, hipStream_t s);
 hipError_t launch_split(const Ctx& ctx, const SplitOp& op, hipStream_t s);
 // Workgroups (of 4 wavefronts) along x of a persistent launch of `kernel`
 // that needs `waves` wavefronts per grid row, with gy grid rows: about

@@ -84,22 +84,33 @@ __global__ __launch_bounds__(256) void permute_kernel(Ctx ctx, PermuteOp op) {
 
 // dst (complex128) += root of every in-flight slice, one slice after the
 // other in slice order: the FP64 sum has the same rounding whatever the batch.
+// A call's first batch starts from zero, so no launch clears dst before it,
+// and where one workgroup holds all of dst it advances the batch counter too.
 template <typename T>
 __global__ __launch_bounds__(256) void accum_kernel(Ctx ctx, AccumOp op) {
   using V = typename C2<T>::t;
   const int64_t o = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (o >= op.n) return;
-  GMEM double2* D = reinterpret_cast<GMEM double2*>(resolve(ctx, op.dst, 0, 0, 16));
-  double2 d = ld(D + o);
-  for (int z = 0; z < ctx.n_batch; z++) {
-    const int64_t sid = slice_id(ctx, z);
-    if (sid < 0) continue;
-    GMEM const V* S = reinterpret_cast<GMEM const V*>(resolve(ctx, op.src, z, sid, sizeof(V)));
-    const V s = ld(S + o);
-    d.x += (double)s.x;
-    d.y += (double)s.y;
+  const int64_t cnt = *reinterpret_cast<CMEM const int64_t*>(ctx.ws + ctx.counter_off);
+  if (o < op.n) {
+    GMEM double2* D = reinterpret_cast<GMEM double2*>(resolve(ctx, op.dst, 0, 0, 16));
+    double2 d;
+    d.x = 0;
+    d.y = 0;
+    if (cnt > 0) d = ld(D + o);
+    for (int z = 0; z < ctx.n_batch; z++) {
+      const int64_t sid = slice_id(ctx, z);
+      if (sid < 0) continue;
+      GMEM const V* S = reinterpret_cast<GMEM const V*>(resolve(ctx, op.src, z, sid, sizeof(V)));
+      const V s = ld(S + o);
+      d.x += (double)s.x;
+      d.y += (double)s.y;
+    }
+    st(D + o, d);
   }
-  st(D + o, d);
+  if (op.advance) {
+    __syncthreads();                         // every wavefront has read the counter
+    if (threadIdx.x == 0) *reinterpret_cast<GMEM int64_t*>(ctx.ws + ctx.counter_off) = cnt + 1;
+  }
 }
 
 __global__ void counter_kernel(Ctx ctx, int64_t value, int add) {

@@ -721,7 +721,8 @@ static uint64_t allocate(Prog& prog) {
       case OpKind::Accum: fix(op.accum.src); fix(op.accum.dst); break;
       case OpKind::Permute: fix(op.perm.src); fix(op.perm.dst); break;
       case OpKind::Split: fix(op.split.src); fix(op.split.dst); break;
-      case OpKind::Tiny: fix_tiny(op); break;
+      case OpKind::Tiny:
+      case OpKind::Scatter: fix_tiny(op); break;
       default: break;
     }
   }

@@ -15,12 +15,12 @@
 
 namespace tn {
 
-enum class OpKind { Row, RowReduce, Gemm, Accum, Permute, Fill, Counter, Split, Tiny };
+enum class OpKind { Row, RowReduce, Gemm, Accum, Permute, Fill, Counter, Split, Tiny, Scatter };
 
 enum KernelClass { kRow = 0, kSplitK = 1, kGemm = 2, kGemmSplitK = 3 };
 
-// One launch of the small-contraction kernel: its blob, and what the host
-// still needs to know about it.
+// One launch of the small-contraction kernel, or of the gradient scatter
+// (n_groups entries): its blob, and what the host still needs to know about it.
 struct TinyLaunch {
   std::vector<char> blob;
   uint32_t n_groups = 0, threads = 0, lds_bytes = 0;

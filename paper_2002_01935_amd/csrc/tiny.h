@@ -34,12 +34,13 @@ struct TinyDir {
   uint32_t pad;
 };
 
-// Contractions first .. of one level, largest thread count first: cnt[i] of
-// them on 2^(10 - i) threads each.
+// One level: its contractions in falling order of their thread counts 2^10 ..
+// 2^2, so that each starts at a multiple of its own count.  In units of four
+// threads: class c (2^(10 - c) threads each) ends at end[c] and begins with
+// contraction first[c]; end[kTinyClasses - 1] is the level's total.
 struct TinyLevel {
-  uint16_t first;
-  uint16_t cnt[kTinyClasses];
-  uint16_t pad[2];
+  uint16_t end[kTinyClasses], first[kTinyClasses];
+  uint16_t pad[6];
 };
 
 // 2^n_bits values copied to LDS: from pointer-table slot `src` (kind 0) or
@@ -72,7 +73,18 @@ struct TinyOp {
   uint64_t oa, ob, ka, kb;
 };
 
-static_assert(sizeof(TinyDir) == 32 && sizeof(TinyLevel) == 24 && sizeof(TinyLoad) == 8, "table layout");
+// One leaf gradient of a scatter launch: the cotangent at arena offset
+// 256 * src (2^n_bits values, compact) is added into pointer-table slot
+// `slot`, bit i at position pos[i], in the block of each in-flight slice.
+struct ScatterEntry {
+  uint32_t src, slot;
+  uint8_t n_bits, n_slice;
+  uint8_t slice_bit[kMaxSliceTerms], slice_pos[kMaxSliceTerms];
+  uint8_t pos[14];
+};
+
+static_assert(sizeof(ScatterEntry) == 40, "table layout");
+static_assert(sizeof(TinyDir) == 32 && sizeof(TinyLevel) == 48 && sizeof(TinyLoad) == 8, "table layout");
 static_assert(sizeof(TinyOp) == 48 && sizeof(TinyExt) % 8 == 0, "table layout");
 
 // Blob sizes the kernel is instantiated for (bytes of kernel argument).

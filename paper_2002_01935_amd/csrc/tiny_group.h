@@ -9,7 +9,7 @@
 // costs; above that, the launch spreads the work over many compute units.
 constexpr int kTinyWorkBits = 12;
 constexpr int kTinyTensorBits = 10;
-constexpr int kTinyGroupOps = 200;         // contractions of one group (tables of that many fit below)
+constexpr int kTinyGroupOps = 170;         // contractions of one group (tables of that many fit below)
 constexpr int kTinyGroupTable = 16384;     // bytes of their table and the levels'
 constexpr int kTinyGroupLds = 61440;       // bytes of LDS, tables included
 
@@ -350,12 +350,16 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
         d.n_levels = (uint32_t)item[ops.back()].level + 1;
         std::vector<TinyLevel> lev(d.n_levels);
         std::memset(lev.data(), 0, lev.size() * sizeof(TinyLevel));
-        for (size_t j = ops.size(); j-- > 0;) lev[(size_t)item[ops[j]].level].first = (uint16_t)j;
-        for (int i : ops) lev[(size_t)item[i].level].cnt[kTinyMaxThreadBits - thread_bits(item[i])]++;
-        for (auto& l : lev) {
-          uint32_t t = 0;
-          for (int c = 0; c < kTinyClasses; c++) t += (uint32_t)l.cnt[c] << (kTinyMaxThreadBits - c);
-          while (max_threads < t && max_threads < 512) max_threads *= 2;
+        size_t j = 0;
+        for (uint32_t l = 0; l < d.n_levels; l++) {
+          uint32_t units = 0;
+          for (int c = 0; c < kTinyClasses; c++) {
+            lev[l].first[c] = (uint16_t)j;
+            for (; j < ops.size() && item[ops[j]].level == (int)l && thread_bits(item[ops[j]]) == kTinyMaxThreadBits - c; j++)
+              units += 1u << (kTinyMaxThreadBits - c - 2);
+            lev[l].end[c] = (uint16_t)units;
+          }
+          while (max_threads < 4 * units && max_threads < 512) max_threads *= 2;
         }
         put(lev.data(), lev.size() * sizeof(TinyLevel));
         align();
@@ -444,12 +448,37 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
     out.ops.push_back(prog.ops[i]);
   }
   launch_at(seq);
+  // the gradient copies, in launches of up to as many entries as a blob holds
+  std::vector<int> copies;
   for (int i = 0; i < nops; i++)
-    if (at_end(i)) out.ops.push_back(prog.ops[i]);
+    if (at_end(i)) copies.push_back(i);
+  constexpr size_t kMost = kTinyBlobLarge / sizeof(ScatterEntry);
+  for (size_t at = 0; at < copies.size(); at += kMost) {
+    auto L = std::make_shared<TinyLaunch>();
+    Op op;
+    op.kind = OpKind::Scatter;
+    for (size_t j = at; j < std::min(copies.size(), at + kMost); j++) {
+      const Op& o = prog.ops[copies[j]];
+      ScatterEntry e;
+      std::memset(&e, 0, sizeof e);
+      e.slot = (uint32_t)o.perm.dst.slot;
+      e.n_bits = (uint8_t)o.perm.n_bits;
+      e.n_slice = (uint8_t)o.perm.dst.n_slice;
+      std::memcpy(e.slice_bit, o.perm.dst.slice_bit, sizeof e.slice_bit);
+      std::memcpy(e.slice_pos, o.perm.dst.slice_pos, sizeof e.slice_pos);
+      for (int i = 0; i < o.perm.n_bits; i++) e.pos[i] = (uint8_t)o.perm.dst_pos[i];
+      L->reads.push_back({(uint32_t)L->blob.size(), (int)o.perm.src.off});
+      L->blob.insert(L->blob.end(), (const char*)&e, (const char*)&e + sizeof e);
+      L->n_groups++;
+      op.node = o.node;
+    }
+    op.tiny = L;
+    out.ops.push_back(op);
+  }
   // lifetimes in the new order
   for (int i = 0; i < (int)out.ops.size(); i++) {
     Op& op = out.ops[i];
-    if (op.kind == OpKind::Tiny) {
+    if (op.kind == OpKind::Tiny || op.kind == OpKind::Scatter) {
       auto touch = [&](int b) { Ref r = buf_ref(b); out.touch(r, i); };
       for (auto& x : op.tiny->reads) touch(x.second);
       for (auto& x : op.tiny->writes) touch(x.second);

@@ -2,11 +2,17 @@
 // group.  Included inside namespace tn after rowops.h.
 #pragma once
 
-// Offset of the low n bits of v through a nibble list of positions (absent
-// bits land at kTinyAbsent, above every LDS operand, and are masked off).
+// Offset of the low n <= 10 bits of v through a nibble list of positions
+// (absent bits land at kTinyAbsent, above every LDS operand, and are masked
+// off).  The list is shifted through two 32-bit registers.
 __device__ __forceinline__ uint32_t nibbles(uint32_t v, uint64_t list, int n) {
-  uint32_t off = 0;
-  for (int i = 0; i < n; i++) off |= ((v >> i) & 1u) << ((uint32_t)(list >> (4 * i)) & 15u);
+  uint32_t off = 0, lo = (uint32_t)list, hi = (uint32_t)(list >> 32);
+  for (int i = 0; i < n; i++) {
+    off |= (v & 1u) << (lo & 15u);
+    v >>= 1;
+    lo = (lo >> 4) | (hi << 28);
+    hi >>= 4;
+  }
   return off & ((1u << kTinyAbsent) - 1u);
 }
 
@@ -50,46 +56,53 @@ __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g,
     }
   }
   __syncthreads();
-  const TinyOp* ops = reinterpret_cast<const TinyOp*>(smem + d.ops_off);
   for (uint32_t l = 0; l < d.n_levels; l++) {
-    const TinyLevel* L = reinterpret_cast<const TinyLevel*>(smem) + l;
-    uint32_t total = 0;
-    for (int c = 0; c < kTinyClasses; c++) total += (uint32_t)L->cnt[c] << (kTinyMaxThreadBits - c);
+    // the level's record in three 128-bit reads: 16-bit ends, then firsts
+    const u4* L = reinterpret_cast<const u4*>(smem) + 3 * l;
+    const u4 w0 = L[0], w1 = L[1], w2 = L[2];
+    const uint32_t w[9] = {w0[0], w0[1], w0[2], w0[3], w1[0], w1[1], w1[2], w1[3], w2[0]};
+    const uint32_t total = 4 * (w[4] & 0xFFFFu);
     for (uint32_t t0 = 0; t0 < total; t0 += nt) {
-      // this thread's contraction and its place in it: thread counts are
-      // powers of two in falling order, so every contraction starts at a
-      // multiple of its own count
-      uint32_t r = t0 + tid, op_i = L->first;
-      bool found = false;
-      for (int c = 0; c < kTinyClasses; c++) {
-        const uint32_t n = L->cnt[c], s = kTinyMaxThreadBits - c;
-        if (!found) {
-          if (r < (n << s)) {
-            op_i += r >> s;
-            r &= (1u << s) - 1u;
-            found = true;
-          } else {
-            r -= n << s;
-            op_i += n;
-          }
+      // this thread's contraction and its place in it
+      const uint32_t t = t0 + tid, unit = t >> 2;
+      uint32_t start = 0, op_i = w[4] >> 16, s = kTinyMaxThreadBits;
+#pragma unroll
+      for (int c = 0; c < kTinyClasses - 1; c++) {
+        const uint32_t end = (c & 1) ? w[c >> 1] >> 16 : w[c >> 1] & 0xFFFFu;
+        const int f = kTinyClasses + c + 1;                        // first[c + 1] among the 16-bit values
+        const uint32_t nf = (f & 1) ? w[f >> 1] >> 16 : w[f >> 1] & 0xFFFFu;
+        if (unit >= end) {
+          start = end;
+          op_i = nf;
+          s = kTinyMaxThreadBits - 1 - c;
         }
       }
-      const TinyOp* op = ops + (found ? op_i : L->first);
-      const int n_out = op->n_out, n_k = op->n_k, ks = op->ks, conj = op->conj;
-      const uint64_t ka = op->ka, kb = op->kb;
+      const bool found = t < total;
+      uint32_t r = t - 4 * start;
+      op_i = found ? op_i + (r >> s) : 0u;
+      r &= (1u << s) - 1u;
+      const u4* P = reinterpret_cast<const u4*>(smem + d.ops_off) + 3 * op_i;
+      const u4 p0 = P[0], p1 = P[1], p2 = P[2];
+      // TinyOp: dst | a, b | c, n_out, n_k | ks, conj, dst_kind, lds_c | oa | ob | ka | kb
+      const uint32_t dst = p0[0], a_lds = p0[1] & 0xFFFFu, b_lds = p0[1] >> 16, c_lds = p0[2] & 0xFFFFu;
+      const int n_out = (p0[2] >> 16) & 0xFF, n_k = p0[2] >> 24;
+      const int ks = p0[3] & 0xFF, conj = (p0[3] >> 8) & 0xFF;
+      const uint32_t dst_kind = (p0[3] >> 16) & 0xFF, lds_c = p0[3] >> 24;
+      const uint64_t oa = p1[0] | uint64_t(p1[1]) << 32, ob = p1[2] | uint64_t(p1[3]) << 32;
+      const uint64_t ka = p2[0] | uint64_t(p2[1]) << 32, kb = p2[2] | uint64_t(p2[3]) << 32;
       const int kk = n_k - ks;
       const T ca = (conj & 1) ? T(-1) : T(1), cb = (conj & 2) ? T(-1) : T(1);
       const uint32_t o = r >> ks, q = r & ((1u << ks) - 1u);
       const bool active = found && (o >> n_out) == 0;
-      const V* A = data + op->a + nibbles(o, op->oa, n_out) + nibbles(q, ka >> (4 * kk), ks);
-      const V* B = data + op->b + nibbles(o, op->ob, n_out) + nibbles(q, kb >> (4 * kk), ks);
+      const V* A = data + a_lds + nibbles(o, oa, n_out) + nibbles(q, ka >> (4 * kk), ks);
+      const V* B = data + b_lds + nibbles(o, ob, n_out) + nibbles(q, kb >> (4 * kk), ks);
       V acc;
       acc.x = 0;
       acc.y = 0;
       if (active) {
         // four summed values at a time: their loads are independent
-        const uint32_t a0 = kk >= 1 ? nibbles(1, ka, 1) : 0u, b0 = kk >= 1 ? nibbles(1, kb, 1) : 0u;
-        const uint32_t a1 = kk >= 2 ? nibbles(1, ka >> 4, 1) : 0u, b1 = kk >= 2 ? nibbles(1, kb >> 4, 1) : 0u;
+        const uint32_t a0 = kk >= 1 ? 1u << (ka & 15) : 0u, b0 = kk >= 1 ? 1u << (kb & 15) : 0u;
+        const uint32_t a1 = kk >= 2 ? 1u << ((ka >> 4) & 15) : 0u, b1 = kk >= 2 ? 1u << ((kb >> 4) & 15) : 0u;
         for (uint32_t j = 0; j < (1u << kk); j += 4) {
           const uint32_t xa = kk > 2 ? nibbles(j >> 2, ka >> 8, kk - 2) : 0u, xb = kk > 2 ? nibbles(j >> 2, kb >> 8, kk - 2) : 0u;
           V a[4], b[4];
@@ -115,10 +128,10 @@ __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g,
         }
       }
       if (active && q == 0) {
-        if (op->lds_c) data[op->c + o] = acc;
-        if (op->dst_kind) {
-          const uint64_t base = op->dst_kind == 1 ? ctx.ws + ctx.arena_off + uint64_t(z) * ctx.arena_stride + 256 * uint64_t(op->dst)
-                                                  : ptrs[op->dst];
+        if (lds_c) data[c_lds + o] = acc;
+        if (dst_kind) {
+          const uint64_t base = dst_kind == 1 ? ctx.ws + ctx.arena_off + uint64_t(z) * ctx.arena_stride + 256 * uint64_t(dst)
+                                                  : ptrs[dst];
           st(reinterpret_cast<GMEM V*>(base) + o, acc);
         }
       }

@@ -139,12 +139,16 @@ struct SplitOp {
   uint32_t j_off[4];          // set at launch: source offset of summed values 0..3
 };
 
-// Fixed-order FP64 accumulation of each in-flight slice's root into dst.
+// Fixed-order FP64 accumulation of each in-flight slice's root into dst; the
+// first batch of a call overwrites it.
 struct AccumOp {
   Ref src;                 // root value (per slice, arena)
   Ref dst;                 // complex128 accumulator (pointer table slot)
   int64_t n;               // elements
+  int32_t advance;         // a single workgroup (n <= kAccumAdvance) also advances the batch counter
+  int32_t pad;
 };
+constexpr int kAccumAdvance = 256;
 
 // Copy a tensor between layouts (general bit permutation), with optional
 // accumulation into the destination; used for leaf gradients and conversions.
