@@ -20,22 +20,24 @@ struct Operand {
   bool leaf = false;
   int id = -1;
   Ref ref;
-  std::vector<int> pos;              // positions of its bits, ascending
+  int n = 0;
+  int8_t pos[kTinyTensorBits] = {};  // positions of its bits, ascending
+  int lds = 0;                       // LDS element offset
 };
 
 struct Item {
   int op = -1;                       // index in the program
   Operand a, b;
-  int c = -1, n_out = 0, n_k = 0;
+  int c = -1, c_lds = 0, n_out = 0, n_k = 0;
   uint64_t oa = 0, ob = 0, ka = 0, kb = 0;
   int conj = 0;
   bool split = false;                // a contraction of the split-K kernel
   int group = -1, stage = 0, level = 0;
 };
 
-inline int rank_of(const std::vector<int>& pos, int p) {
-  for (size_t i = 0; i < pos.size(); i++)
-    if (pos[i] == p) return (int)i;
+inline int rank_of(const Operand& o, int p) {
+  for (int i = 0; i < o.n; i++)
+    if (o.pos[i] == p) return i;
   return kTinyAbsent;
 }
 
@@ -77,12 +79,14 @@ inline bool describe(const Op& op, bool gemm_too, bool splits, Item& it) {
     o.leaf = r.kind == 0;
     o.id = o.leaf ? r.slot : (int)r.off;
     o.ref = r;
-    for (int i = 0; i < n_out; i++) if (c[i] >= 0) o.pos.push_back(c[i]);
-    for (int i = 0; i < n_k; i++) o.pos.push_back(k[i]);
-    std::sort(o.pos.begin(), o.pos.end());
-    if ((int)o.pos.size() > kTinyTensorBits) return false;
-    for (int i = 0; i < n_out; i++) on |= uint64_t(c[i] < 0 ? kTinyAbsent : rank_of(o.pos, c[i])) << (4 * i);
-    for (int i = 0; i < n_k; i++) kn |= uint64_t(rank_of(o.pos, k[i])) << (4 * i);
+    int n = n_k;
+    for (int i = 0; i < n_out; i++) n += c[i] >= 0;
+    if (n > kTinyTensorBits) return false;
+    for (int i = 0; i < n_out; i++) if (c[i] >= 0) o.pos[o.n++] = c[i];
+    for (int i = 0; i < n_k; i++) o.pos[o.n++] = k[i];
+    std::sort(o.pos, o.pos + o.n);
+    for (int i = 0; i < n_out; i++) on |= uint64_t(c[i] < 0 ? kTinyAbsent : rank_of(o, c[i])) << (4 * i);
+    for (int i = 0; i < n_k; i++) kn |= uint64_t(rank_of(o, k[i])) << (4 * i);
     return true;
   };
   it.n_out = n_out;
@@ -148,8 +152,13 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
   }
   std::vector<int> rep(nops);
   std::vector<std::vector<int>> members;                   // per group, program order
-  std::vector<std::map<std::pair<int, int>, int>> lds;     // per group: (leaf?, id) -> LDS element offset
   std::vector<uint32_t> lds_elems;
+  // values by key: buffers, then leaves; `seen` marks those of the group at hand
+  auto key_of = [&](const tiny_detail::Operand& o) { return o.leaf ? nbuf + o.id : o.id; };
+  struct Val { int size = 0, first = 0, last = 0, lds = 0; };
+  std::vector<Val> vals((size_t)nbuf + p->n_leaves);
+  std::vector<int> seen((size_t)nbuf + p->n_leaves, -1);
+  int mark = 0;
   auto find = [&](int x) { while (rep[x] != x) x = rep[x] = rep[rep[x]]; return x; };
   auto inputs = [&](int i, auto&& f) {
     if (small[i]) {
@@ -182,52 +191,67 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
       }
     }
     members.clear();
-    std::map<int, int> ids;
+    std::vector<int> ids(nops, -1);
     for (int i = 0; i < nops; i++)
       if (small[i]) {
-        auto it = ids.emplace(find(i), (int)members.size());
-        if (it.second) members.emplace_back();
-        item[i].group = it.first->second;
+        int& id = ids[(size_t)find(i)];
+        if (id < 0) {
+          id = (int)members.size();
+          members.emplace_back();
+        }
+        item[i].group = id;
         members[(size_t)item[i].group].push_back(i);
       }
-    lds.assign(members.size(), {});
     lds_elems.assign(members.size(), 0);
     bool fits = true;
     std::vector<int> below(nops, 0), above(nops, 0);
     for (size_t g = 0; g < members.size(); g++) {
       // LDS offsets from lifetimes in levels (first fit): loads live from the
       // start, outputs from their level, until their last reading level
-      struct Val { int size, first, last; };
-      std::map<std::pair<int, int>, Val> vals;
-      int levels = 0;
+      std::vector<int> keys;
+      int levels = 0, ext = 0;
+      mark++;
       for (int i : members[g]) {
         levels = std::max(levels, item[i].level + 1);
         for (const tiny_detail::Operand* o : {&item[i].a, &item[i].b}) {
-          auto key = std::make_pair(o->leaf ? 1 : 0, o->id);
-          auto it = vals.emplace(key, Val{1 << o->pos.size(), -1, item[i].level}).first;
-          it->second.last = std::max(it->second.last, item[i].level);
+          const int k = key_of(*o);
+          if (seen[k] != mark) {
+            seen[k] = mark;
+            keys.push_back(k);
+            vals[k] = Val{1 << o->n, -1, 0, 0};
+            ext++;
+          }
+          vals[k].last = std::max(vals[k].last, item[i].level);
         }
-        vals[{0, item[i].c}] = Val{1 << item[i].n_out, item[i].level, item[i].level};
+        seen[item[i].c] = mark;
+        keys.push_back(item[i].c);
+        vals[item[i].c] = Val{1 << item[i].n_out, item[i].level, item[i].level, 0};
       }
-      std::vector<std::vector<std::pair<int, int>>> born((size_t)levels + 1), dies((size_t)levels + 1);
-      for (auto& v : vals) { born[(size_t)(v.second.first + 1)].push_back(v.first); dies[(size_t)(v.second.last + 1)].push_back(v.first); }
-      std::map<int, int> used;
+      std::vector<std::vector<int>> born((size_t)levels + 1), dies((size_t)levels + 1);
+      for (int k : keys) { born[(size_t)(vals[k].first + 1)].push_back(k); dies[(size_t)(vals[k].last + 1)].push_back(k); }
+      std::vector<std::pair<int, int>> used;               // (offset, size), ascending
       int peak = 0;
       for (int t = 0; t <= levels; t++) {
-        for (auto& key : born[(size_t)t]) {
-          const int sz = (vals[key].size + 3) / 4 * 4;
+        for (int k : born[(size_t)t]) {
+          const int sz = (vals[k].size + 3) / 4 * 4;
           int cur = 0;
-          for (auto& u : used) { if (u.first - cur >= sz) break; cur = std::max(cur, u.first + u.second); }
-          used[cur] = sz;
-          lds[g][key] = cur;
+          size_t at = 0;
+          for (; at < used.size() && used[at].first - cur < sz; at++) cur = used[at].first + used[at].second;
+          used.insert(used.begin() + at, {cur, sz});
+          vals[k].lds = cur;
           peak = std::max(peak, cur + sz);
         }
-        for (auto& key : dies[(size_t)t]) used.erase(lds[g][key]);
+        for (int k : dies[(size_t)t])
+          used.erase(std::lower_bound(used.begin(), used.end(), std::make_pair(vals[k].lds, 0)));
+      }
+      for (int i : members[g]) {
+        item[i].a.lds = vals[key_of(item[i].a)].lds;
+        item[i].b.lds = vals[key_of(item[i].b)].lds;
+        item[i].c_lds = vals[item[i].c].lds;
       }
       lds_elems[g] = (uint32_t)peak;
       const int table = (levels * (int)sizeof(TinyLevel) + 15) / 16 * 16 + (int)(members[g].size() * sizeof(TinyOp));
-      int loads = 0;
-      for (auto& v : vals) loads += v.second.first < 0 ? (int)(sizeof(TinyLoad) + sizeof(TinyExt)) : 0;
+      const int loads = ext * (int)(sizeof(TinyLoad) + sizeof(TinyExt));
       if (members[g].size() <= (size_t)kTinyGroupOps && table <= kTinyGroupTable &&
           table + loads + 64 <= kTinyBlobLarge && table + 64 + peak * p->elem_bytes <= kTinyGroupLds)
         continue;
@@ -364,19 +388,24 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
         put(lev.data(), lev.size() * sizeof(TinyLevel));
         align();
         d.ops_off = (uint32_t)blob.size() - d.tab_off;
-        std::map<std::pair<int, int>, const tiny_detail::Operand*> ext;
+        std::vector<const tiny_detail::Operand*> ext;
+        mark++;
         for (int i : ops) {
           const Item& it = item[i];
           const uint32_t here = (uint32_t)blob.size();
           TinyOp t;
           std::memset(&t, 0, sizeof t);
           auto off = [&](const tiny_detail::Operand& o) {
-            if (o.leaf || !small[producer[o.id]] || item[producer[o.id]].group != g) ext[{o.leaf ? 1 : 0, o.id}] = &o;
-            return (uint16_t)lds[(size_t)g][{o.leaf ? 1 : 0, o.id}];
+            const int k = key_of(o);
+            if ((o.leaf || !small[producer[o.id]] || item[producer[o.id]].group != g) && seen[k] != mark) {
+              seen[k] = mark;
+              ext.push_back(&o);
+            }
+            return (uint16_t)o.lds;
           };
           t.a = off(it.a);
           t.b = off(it.b);
-          t.c = (uint16_t)lds[(size_t)g][{0, it.c}];
+          t.c = (uint16_t)it.c_lds;
           t.n_out = (uint8_t)it.n_out;
           t.n_k = (uint8_t)it.n_k;
           t.ks = (uint8_t)split_bits(it);
@@ -400,13 +429,13 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
         d.ld_off = (uint32_t)blob.size();
         d.n_loads = (uint32_t)ext.size();
         std::vector<TinyExt> exts;
-        for (auto& e : ext) {
-          const tiny_detail::Operand& o = *e.second;
+        for (const tiny_detail::Operand* e : ext) {
+          const tiny_detail::Operand& o = *e;
           TinyLoad ld;
-          ld.lds = (uint16_t)lds[(size_t)g][e.first];
-          ld.n_bits = (uint8_t)o.pos.size();
+          ld.lds = (uint16_t)o.lds;
+          ld.n_bits = (uint8_t)o.n;
           bool plain = o.ref.n_slice == 0;
-          for (size_t i = 0; i < o.pos.size(); i++) plain = plain && o.pos[i] == (int)i;
+          for (int i = 0; i < o.n; i++) plain = plain && o.pos[i] == i;
           if (!o.leaf) {
             ld.kind = 1;
             ld.src = 0;
@@ -420,7 +449,7 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
             TinyExt x;
             std::memset(&x, 0, sizeof x);
             x.ref = o.ref;
-            for (size_t i = 0; i < o.pos.size(); i++) x.pos[i] = (int8_t)o.pos[i];
+            std::memcpy(x.pos, o.pos, (size_t)o.n);
             exts.push_back(x);
           }
           put(&ld, sizeof ld);
