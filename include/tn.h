@@ -316,14 +316,16 @@ int tn_contract_sliced_noalloc(tn_plan_t plan, const void* const* leaves, int64_
  * needs many contractions).  A batch takes n_plans compiled, unsliced plans
  * of one precision (TN_E_UNSUPPORTED for a sliced plan, TN_E_INVALID for
  * mixed precisions); it copies their programs (with their tile choices at
- * this time), so the plans may be destroyed afterwards.  Each network's
- * contractions with at most 2^14 (outputs x summed values) run inside one
- * interpreter kernel, one workgroup per network, in the network's own order;
- * the others with the ordinary kernels between the interpreter's launches.
- * The result of network j is its tn_contract result.
+ * this time), so the plans may be destroyed afterwards.  The groups of small
+ * contractions at the bottom of all networks run in one launch; the
+ * contractions that remain are sorted into levels by their dependences, and
+ * a level's contractions with at most 2^22 (outputs x summed values), of all
+ * networks, run in one launch, the others with the ordinary kernels.
+ * The result of network j is its tn_contract result, up to the rounding of
+ * sums taken in another order.
  *
- * tn_batch_info: workspace bytes, number of interpreter launches (levels),
- * number of contractions the interpreter runs, and launches per call.
+ * tn_batch_info: workspace bytes, number of levels, number of contractions
+ * that run in the shared launches, and launches per call.
  *
  * tn_batch_prepare: writes the batch's tables (contraction descriptors and
  * per-network launch contexts) into `workspace` and captures the graph for

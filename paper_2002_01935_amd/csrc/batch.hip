@@ -2,17 +2,17 @@
 //
 // Workloads such as the QAOA energy (Sec. 4.5: one light-cone network per
 // edge) or a batch of sampled bitstrings (Sec. 4.7.3) are many small networks
-// whose contractions are mostly tiny: gate merges of a few dozen elements.
-// Launched one kernel per pairwise contraction, such a network is bound by
-// launch latency (about 190 launches per QAOA term).  Here each network's
-// forward program (in its own order, so its arena stays valid) is cut into
-// segments of tiny contractions separated by the contractions that are
-// worth a launch of their own.  Segment L of every network runs in one launch
-// of the interpreter kernel, one workgroup per network executing its tiny
-// contractions one after another (a workgroup barrier between them); then the
-// large contractions that follow segment L in each network are launched with
-// the ordinary kernels; then segment L + 1.  The whole sequence is captured
-// once per workspace into a HIP graph and replayed by tn_batch_contract.
+// whose contractions are mostly tiny.  Launched one kernel per pairwise
+// contraction they are bound by launch latency.  Here the groups of small
+// contractions at the bottom of all networks (tiny.h) run in one launch, a
+// workgroup per group.  The contractions that remain in each network are
+// sorted into levels: one per chain of dependences, where two of a network's
+// ops depend on each other if one writes arena memory that the other touches
+// (its arena was laid out for its own order).  A level's medium-sized
+// contractions, of all networks, run in one launch whose workgroups look up
+// their contraction in a table; its large ones are launched with the ordinary
+// kernels, on parallel branches.  The whole sequence is captured once per
+// workspace into a HIP graph and replayed by tn_batch_contract.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,140 +37,146 @@ namespace tn {
 #include "rowops.h"
 #include "tiny_kernel.h"
 
-constexpr int kTinyBits = 16;       // bit-list capacity of a tiny contraction
-constexpr int kTinyWorkBits = 16;   // log2 (outputs x summed values) of the largest one
-constexpr int kTinyThreads = 256;
+constexpr int kLevelBits = 24;      // bit-list capacity of a medium contraction
+constexpr int kLevelWorkBits = 22;  // log2 (outputs x summed values) of the largest one
+constexpr int kLevelThreads = 256;
 // parallel branches of a level's large contractions in the captured graph
 // (one per hardware queue a process gets by default)
 constexpr int kBranches = 4;
 
-// One tiny pairwise contraction: for each of 2^n_out outputs,
-//   C[o] (+)= sum over 2^n_k summed values of opA(A[o, k]) * opB(B[o, k])
-// (opX = complex conjugate when conj_x), or C[o] (+)= opA(A[o]) without B.
-// Output bit j sits at position oa[j] / ob[j] / oc[j] of A / B / C (-1:
-// absent from that operand), summed bit j at ka[j] / kb[j].
-struct BatchOp {
+// One medium contraction: for each of 2^n_out outputs,
+//   C[o] = sum over 2^n_k summed values of opA(A[o, k]) * opB(B[o, k])
+// (opX = complex conjugate when conj_x), or C[o] = A[o] without B.  Output bit
+// j sits at position oa[j] / ob[j] / oc[j] of A / B / C (-1: absent from that
+// operand), summed bit j at ka[j] / kb[j].
+struct LevelOp {
   Ref a, b, c;
-  int32_t n_out, n_k;
-  int32_t has_b, conj_a, conj_b, accumulate;
-  int8_t oa[kTinyBits], ob[kTinyBits], oc[kTinyBits];
-  int8_t ka[kTinyBits], kb[kTinyBits];
+  uint32_t net;
+  int32_t n_out, n_k, mode;
+  int32_t has_b, conj_a, conj_b, pad;
+  int8_t oa[kLevelBits], ob[kLevelBits], oc[kLevelBits], ka[kLevelBits], kb[kLevelBits];
 };
-static_assert(offsetof(BatchOp, oa) % 4 == 0 && sizeof(BatchOp) % 8 == 0, "BatchOp layout");
+static_assert(offsetof(LevelOp, oa) % 4 == 0 && sizeof(LevelOp) % 8 == 0, "LevelOp layout");
 
-__device__ __forceinline__ int tpos(CMEM const int8_t* list, int i) {
-  const uint32_t w = reinterpret_cast<CMEM const uint32_t*>(list)[i >> 2];
-  return (int8_t)(w >> (8 * (i & 3)));
+// A workgroup's contraction and its block of that contraction's outputs.
+struct LevelBlock {
+  uint32_t op, block;
+};
+
+// Threads of one output (LevelOp::mode): one thread, one wavefront (lanes over
+// the lowest six summed bits) or the whole workgroup (the lowest eight).
+enum { kPerThread = 0, kPerWave = 1, kPerGroup = 2 };
+
+// A list of up to 24 byte positions in registers (uniform: scalar loads).
+struct PosList {
+  uint64_t w[3];
+};
+__device__ __forceinline__ PosList pos_list(CMEM const int8_t* p) {
+  PosList l;
+#pragma unroll
+  for (int i = 0; i < 3; i++) {
+    CMEM const uint32_t* q = reinterpret_cast<CMEM const uint32_t*>(p) + 2 * i;
+    l.w[i] = q[0] | uint64_t(q[1]) << 32;
+  }
+  return l;
 }
-
-// Offset of value v's bits in an operand (positions < 0: absent).
-__device__ __forceinline__ uint32_t tdeposit(uint32_t v, CMEM const int8_t* list, int first, int n) {
+// The list from entry `first` on (first < 8 or a multiple of 8).
+__device__ __forceinline__ PosList tail(const PosList& l, int first) {
+  PosList r;
+  const int s = 8 * (first & 7);
+  r.w[0] = first >= 8 ? l.w[1] : l.w[0];
+  r.w[1] = first >= 8 ? l.w[2] : l.w[1];
+  r.w[2] = first >= 8 ? 0 : l.w[2];
+  if (s) {
+    r.w[0] = (r.w[0] >> s) | (r.w[1] << (64 - s));
+    r.w[1] = (r.w[1] >> s) | (r.w[2] << (64 - s));
+    r.w[2] >>= s;
+  }
+  return r;
+}
+// Offset of the low n bits of v (positions < 0: absent).
+__device__ __forceinline__ uint32_t place(uint32_t v, PosList l, int n) {
   uint32_t off = 0;
+#pragma unroll 1
   for (int i = 0; i < n; i++) {
-    const int p = tpos(list, first + i);
-    off |= p >= 0 ? ((v >> i) & 1u) << p : 0u;
+    const int p = (int8_t)l.w[0];
+    off |= p >= 0 ? (v & 1u) << p : 0u;
+    v >>= 1;
+    l = tail(l, 1);
   }
   return off;
 }
 
-template <typename V>
-__device__ __forceinline__ V conj_if(V v, int c) {
-  if (c) v.y = -v.y;
-  return v;
-}
-
-// Segment `level` of network blockIdx.x: its tiny contractions in program
-// order.  An output is summed by 2^g threads (g = min(8 - n_out, n_k) when
-// there are fewer than 256 outputs), each over a contiguous run of summed
-// values walked with per-carry offset steps, and the 2^g partial sums are
-// added in a fixed tree order (results do not depend on scheduling).
+// A level's medium contractions of all networks.  Latency bound (a few
+// microseconds of dependent loads); a launch per contraction would pay that
+// and the launch each time.  81 QAOA terms: 12 levels, 60 launches per call in
+// place of 624, 4.56 -> 1.89 ms against one workgroup per network running up
+// to 2^16 multiply-adds per contraction (410 us per launch) between launches.
 template <typename T>
-__global__ __launch_bounds__(kTinyThreads) void tiny_kernel(CMEM const Ctx* ctxs, CMEM const BatchOp* ops,
-                                                            CMEM const int32_t* seg) {
+__global__ __launch_bounds__(kLevelThreads) void level_kernel(CMEM const Ctx* ctxs, CMEM const LevelOp* ops,
+                                                              CMEM const LevelBlock* blocks) {
   using V = typename C2<T>::t;
-  const int net = blockIdx.x;
-  const int begin = seg[2 * net], end = seg[2 * net + 1];
-  if (begin >= end) return;
-  const Ctx ctx = cload(ctxs + net);
-  const int tid = threadIdx.x;
-  __shared__ uint32_t kd[2][kTinyBits];
-  __shared__ V red[kTinyThreads];
-  for (int i = begin; i < end; i++) {
-    CMEM const BatchOp* op = ops + i;
-    const int n_out = op->n_out, n_k = op->n_k, has_b = op->has_b;
-    const int ca = op->conj_a, cb = op->conj_b, accum = op->accumulate;
-    const int g = n_out < 8 ? min(8 - n_out, n_k) : 0;
-    const int walk = n_k - g;
-    const Ref ra = cload(&op->a), rb = cload(&op->b), rc = cload(&op->c);
-    GMEM const V* A = reinterpret_cast<GMEM const V*>(resolve(ctx, ra, 0, 0, sizeof(V)));
-    GMEM const V* B = has_b ? reinterpret_cast<GMEM const V*>(resolve(ctx, rb, 0, 0, sizeof(V))) : nullptr;
-    GMEM V* C = reinterpret_cast<GMEM V*>(resolve(ctx, rc, 0, 0, sizeof(V)));
-    // offset change in A / B when the walk's counter carries into its bit t
-    if (tid < walk) {
-      uint32_t da = 1u << tpos(op->ka, tid), db = has_b ? 1u << tpos(op->kb, tid) : 0u;
-      for (int j = 0; j < tid; j++) {
-        da -= 1u << tpos(op->ka, j);
-        if (has_b) db -= 1u << tpos(op->kb, j);
+  const LevelBlock e = cload(blocks + blockIdx.x);
+  CMEM const LevelOp* op = ops + e.op;
+  const Ctx ctx = cload(ctxs + op->net);
+  const int n_out = op->n_out, n_k = op->n_k, mode = op->mode, has_b = op->has_b;
+  const uint32_t tid = threadIdx.x;
+  const Ref ra = cload(&op->a), rb = cload(&op->b), rc = cload(&op->c);
+  GMEM const V* A = reinterpret_cast<GMEM const V*>(resolve(ctx, ra, 0, 0, sizeof(V)));
+  GMEM const V* B = has_b ? reinterpret_cast<GMEM const V*>(resolve(ctx, rb, 0, 0, sizeof(V))) : A;
+  GMEM V* C = reinterpret_cast<GMEM V*>(resolve(ctx, rc, 0, 0, sizeof(V)));
+  const int ts = mode == kPerThread ? 0 : (mode == kPerWave ? 6 : 8);   // log2 threads per output
+  const uint32_t o = (e.block * kLevelThreads + tid) >> ts, q = tid & ((1u << ts) - 1u);
+  const bool active = (o >> n_out) == 0;
+  const uint32_t oo = active ? o : 0u;
+  const PosList ka = pos_list(op->ka), kb = pos_list(op->kb);
+  V acc;
+  acc.x = 0;
+  acc.y = 0;
+  if (!has_b) {
+    acc = ld(A + place(oo, pos_list(op->oa), n_out));
+  } else {
+    const T ca = op->conj_a ? T(-1) : T(1), cb = op->conj_b ? T(-1) : T(1);
+    GMEM const V* Ao = A + place(oo, pos_list(op->oa), n_out) + place(q, ka, ts);
+    GMEM const V* Bo = B + place(oo, pos_list(op->ob), n_out) + place(q, kb, ts);
+    // the remaining summed bits in order, four values at a time (uniform offsets)
+    const PosList wa = tail(ka, ts), wb = tail(kb, ts);
+    const int walk = n_k - ts;
+    const int lo = walk < 2 ? walk : 2;
+    const uint32_t a0 = walk >= 1 ? 1u << (wa.w[0] & 31) : 0u, b0 = walk >= 1 ? 1u << (wb.w[0] & 31) : 0u;
+    const uint32_t a1 = walk >= 2 ? 1u << ((wa.w[0] >> 8) & 31) : 0u, b1 = walk >= 2 ? 1u << ((wb.w[0] >> 8) & 31) : 0u;
+    const PosList ha = tail(wa, lo), hb = tail(wb, lo);
+    const uint32_t steps = 1u << (walk - lo);
+    for (uint32_t s = 0; s < steps; s++) {
+      const uint32_t xa = place(s, ha, walk - lo), xb = place(s, hb, walk - lo);
+      V a[4], b[4];
+      a[0] = ld(Ao + xa); b[0] = ld(Bo + xb);
+      a[1] = ld(Ao + xa + a0); b[1] = ld(Bo + xb + b0);
+      a[2] = ld(Ao + xa + a1); b[2] = ld(Bo + xb + b1);
+      a[3] = ld(Ao + xa + a0 + a1); b[3] = ld(Bo + xb + b0 + b1);
+#pragma unroll
+      for (int u = 0; u < 4; u++) {
+        a[u].y *= ca;
+        b[u].y *= cb;
+        if (u < 1 || (u < 2 && walk >= 1) || walk >= 2) acc = cfma(acc, a[u], b[u]);
       }
-      kd[0][tid] = da;
-      kd[1][tid] = db;
     }
-    __syncthreads();
-    const uint32_t n_outputs = 1u << n_out, steps = 1u << walk;
-    const uint32_t per_pass = (uint32_t)kTinyThreads >> g;
-    for (uint32_t o0 = 0; o0 < n_outputs; o0 += per_pass) {
-      const uint32_t o = o0 + ((uint32_t)tid >> g);
-      const uint32_t r = (uint32_t)tid & ((1u << g) - 1u);
-      const bool active = o < n_outputs && ((uint32_t)tid >> g) < per_pass;
-      V acc;
-      acc.x = 0;
-      acc.y = 0;
-      if (active) {
-        uint32_t xa = tdeposit(o, op->oa, 0, n_out) + tdeposit(r, op->ka, walk, g);
-        uint32_t xb = has_b ? tdeposit(o, op->ob, 0, n_out) + tdeposit(r, op->kb, walk, g) : 0u;
-        for (uint32_t s = 0; s < steps; s++) {
-          const V a = conj_if(ld(A + xa), ca);
-          if (has_b) {
-            const V b = conj_if(ld(B + xb), cb);
-            acc = cfma(acc, a, b);
-          } else {
-            acc.x += a.x;
-            acc.y += a.y;
-          }
-          if (s + 1 < steps) {
-            const int t = __builtin_ctz(~s);
-            xa += kd[0][t];
-            xb += kd[1][t];
-          }
-        }
-      }
-      if (g > 0) {
-        red[tid] = acc;
-        __syncthreads();
-        for (int w = 1 << (g - 1); w >= 1; w >>= 1) {
-          if ((int)r < w) {
-            V u = red[tid], v = red[tid + w];
-            u.x += v.x;
-            u.y += v.y;
-            red[tid] = u;
-          }
-          __syncthreads();
-        }
-        acc = red[tid];
-      }
-      if (active && r == 0) {
-        GMEM V* dst = C + tdeposit(o, op->oc, 0, n_out);
-        if (accum) {
-          const V p = ld(dst);
-          acc.x += p.x;
-          acc.y += p.y;
-        }
-        st(dst, acc);
-      }
-      if (g > 0) __syncthreads();   // red[] is rewritten by the next pass
-    }
-    __syncthreads();   // this contraction's output is read by the next one
   }
+  if (mode != kPerThread) {                      // fixed order: butterfly, then the wavefronts in order
+    acc.x = wave_sum(acc.x);
+    acc.y = wave_sum(acc.y);
+    if (mode == kPerGroup) {
+      __shared__ V part[kLevelThreads / 64];
+      if ((tid & 63) == 0) part[tid >> 6] = acc;
+      __syncthreads();
+      acc = part[0];
+      for (int w = 1; w < kLevelThreads / 64; w++) {
+        acc.x += part[w].x;
+        acc.y += part[w].y;
+      }
+    }
+  }
+  if (active && q == 0) st(C + place(o, pos_list(op->oc), n_out), acc);
 }
 
 // The small-contraction launches that begin each network's program, all in one
@@ -188,30 +194,27 @@ __global__ __launch_bounds__(512) void tiny_batch_kernel(uint64_t base, CMEM con
   tiny_group<T>(ctx, base + e.blob, (int)e.group, 0, 0, smem);
 }
 
-// Whether op runs inside the interpreter, and its descriptor if so.
-static bool as_tiny(const Op& op, int prec, BatchOp& t) {
+// Whether op is a medium contraction, and its descriptor if so.
+static bool as_level(const Op& op, int prec, LevelOp& t) {
   std::memset(&t, 0, sizeof t);
-  for (int j = 0; j < kTinyBits; j++) t.oa[j] = t.ob[j] = t.oc[j] = t.ka[j] = t.kb[j] = -1;
+  for (int j = 0; j < kLevelBits; j++) t.oa[j] = t.ob[j] = t.oc[j] = t.ka[j] = t.kb[j] = -1;
+  auto fits = [&](int n_out, int n_k) {
+    t.n_out = n_out;
+    t.n_k = n_k;
+    return n_out <= kLevelBits && n_k <= kLevelBits && n_out + n_k <= kLevelWorkBits;
+  };
   if (op.kind == OpKind::Row) {
     const RowOp& r = op.row;
-    if (r.k_split_bits >= 0) return false;
-    t.n_out = r.n_rows + r.n_in;
-    t.n_k = r.n_k;
-    if (t.n_out > kTinyBits || t.n_k > kTinyBits || t.n_out + t.n_k > kTinyWorkBits) return false;
+    if (r.accumulate || !fits(r.n_rows + r.n_in, r.n_k)) return false;
     for (int j = 0; j < r.n_rows; j++) { t.oa[j] = r.row_a[j]; t.ob[j] = r.row_b[j]; t.oc[j] = r.row_c[j]; }
     for (int j = 0; j < r.n_in; j++) { t.ob[r.n_rows + j] = r.in_b[j]; t.oc[r.n_rows + j] = r.in_c[j]; }
     for (int j = 0; j < r.n_k; j++) { t.ka[j] = r.k_a[j]; t.kb[j] = r.k_b[j]; }
     t.a = r.a; t.b = r.b; t.c = r.c;
     t.has_b = 1;
-    t.conj_a = r.conj_a; t.conj_b = r.conj_b; t.accumulate = r.accumulate;
-    return true;
-  }
-  if (op.kind == OpKind::Gemm) {
+    t.conj_a = r.conj_a; t.conj_b = r.conj_b;
+  } else if (op.kind == OpKind::Gemm) {
     const GemmOp& g = op.gemm;
-    if (g.k_split_bits > 0 || g.ab_split) return false;
-    t.n_out = g.n_h + g.n_m + g.n_n;
-    t.n_k = g.n_k;
-    if (t.n_out > kTinyBits || t.n_k > kTinyBits || t.n_out + t.n_k > kTinyWorkBits) return false;
+    if (g.accumulate || g.ab_split || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
     int j = 0;
     for (int i = 0; i < g.n_h; i++, j++) { t.oa[j] = g.a_h[i]; t.ob[j] = g.b_h[i]; t.oc[j] = g.c_h[i]; }
     for (int i = 0; i < g.n_m; i++, j++) { t.oa[j] = g.a_m[i]; t.oc[j] = g.c_m[i]; }
@@ -219,24 +222,87 @@ static bool as_tiny(const Op& op, int prec, BatchOp& t) {
     for (int i = 0; i < g.n_k; i++) { t.ka[i] = g.a_k[i]; t.kb[i] = g.b_k[i]; }
     t.a = g.a; t.b = g.b; t.c = g.c;
     t.has_b = 1;
-    t.conj_a = g.conj_a; t.conj_b = g.conj_b; t.accumulate = g.accumulate;
-    return true;
-  }
-  if (op.kind == OpKind::Permute) {
+    t.conj_a = g.conj_a; t.conj_b = g.conj_b;
+  } else if (op.kind == OpKind::Permute) {
     const PermuteOp& pm = op.perm;
     const int c128 = prec == TN_C128;
-    if (pm.n_bits > kTinyBits || pm.n_bits > kTinyWorkBits || pm.src_c128 != c128 || pm.dst_c128 != c128 ||
-        pm.per_slice_serial)
-      return false;
-    t.n_out = pm.n_bits;
-    t.n_k = 0;
+    if (pm.accumulate || !fits(pm.n_bits, 0) || pm.src_c128 != c128 || pm.dst_c128 != c128 || pm.per_slice_serial) return false;
     for (int j = 0; j < pm.n_bits; j++) { t.oa[j] = pm.src_pos[j]; t.oc[j] = pm.dst_pos[j]; }
     t.a = pm.src; t.c = pm.dst;
-    t.has_b = 0;
-    t.accumulate = pm.accumulate;
-    return true;
+  } else {
+    return false;
   }
-  return false;
+  // short sums by one thread; long ones shared, by a wavefront while there
+  // are outputs enough for a few thousand of them
+  t.mode = t.n_k < 6 || t.n_out >= 14 ? kPerThread : (t.n_k >= 12 && t.n_out <= 8 ? kPerGroup : kPerWave);
+  return true;
+}
+
+// Arena bytes an op reads and writes (elements of eb bytes; operands there are
+// compact); false when that is not known.
+struct ArenaUse {
+  std::vector<std::pair<int64_t, int64_t>> reads, writes;   // [begin, end)
+  bool known = true;
+  bool conflicts(const ArenaUse& later) const {
+    if (!known || !later.known) return true;
+    auto meet = [](const std::vector<std::pair<int64_t, int64_t>>& x, const std::vector<std::pair<int64_t, int64_t>>& y) {
+      for (auto& a : x)
+        for (auto& b : y)
+          if (a.first < b.second && b.first < a.second) return true;
+      return false;
+    };
+    return meet(writes, later.reads) || meet(writes, later.writes) || meet(reads, later.writes);
+  }
+};
+
+static ArenaUse arena_use(const Op& op, int eb) {
+  ArenaUse u;
+  auto add = [&](std::vector<std::pair<int64_t, int64_t>>& v, const Ref& r, int bits, int bytes) {
+    if (r.kind == 1) v.push_back({r.off, r.off + (int64_t(bytes) << bits)});
+  };
+  auto count = [](const int8_t* p, int n) { int c = 0; for (int i = 0; i < n; i++) c += p[i] >= 0; return c; };
+  switch (op.kind) {
+    case OpKind::Row: {
+      const RowOp& r = op.row;
+      const int out = r.n_rows + r.n_in;
+      add(u.reads, r.a, count(r.row_a, r.n_rows) + r.n_k, eb);
+      add(u.reads, r.b, count(r.row_b, r.n_rows) + count(r.in_b, r.n_in) + r.n_k, eb);
+      add(u.writes, r.c, out, eb);
+      if (r.k_split_bits > 0) add(u.writes, r.part, out + r.k_split_bits, eb);
+      break;
+    }
+    case OpKind::RowReduce:
+      add(u.reads, op.row.part, op.row.n_rows + op.row.n_in + op.row.k_split_bits, eb);
+      add(u.writes, op.row.c, op.row.n_rows + op.row.n_in, eb);
+      break;
+    case OpKind::Gemm: {
+      const GemmOp& g = op.gemm;
+      if (g.ab_split) { u.known = false; break; }
+      add(u.reads, g.a, g.n_h + g.n_m + g.n_k, eb);
+      add(u.reads, g.b, g.n_h + g.n_n + g.n_k, eb);
+      add(u.writes, g.c, g.n_h + g.n_m + g.n_n, eb);
+      if (g.k_split_bits > 0) add(u.writes, g.part, g.n_h + g.n_m + g.n_n + g.k_split_bits, eb);
+      break;
+    }
+    case OpKind::Permute:
+      add(u.reads, op.perm.src, op.perm.n_bits, op.perm.src_c128 ? 16 : 8);
+      add(u.writes, op.perm.dst, op.perm.n_bits, op.perm.dst_c128 ? 16 : 8);
+      break;
+    case OpKind::Tiny:
+      for (auto& x : op.tiny->reads) {
+        TinyLoad l;
+        std::memcpy(&l, op.tiny->blob.data() + x.first, sizeof l);
+        u.reads.push_back({256 * (int64_t)l.src, 256 * (int64_t)l.src + (int64_t(eb) << l.n_bits)});
+      }
+      for (auto& x : op.tiny->writes) {
+        TinyOp t;
+        std::memcpy(&t, op.tiny->blob.data() + x.first, sizeof t);
+        if (t.dst_kind == 1) u.writes.push_back({256 * (int64_t)t.dst, 256 * (int64_t)t.dst + (int64_t(eb) << t.n_out)});
+      }
+      break;
+    default: u.known = false;
+  }
+  return u;
 }
 
 }  // namespace tn
@@ -250,16 +316,18 @@ struct tn_batch_s {
   std::vector<int32_t> n_leaves;             // per network
   std::vector<uint64_t> region_off;          // per network: its plan workspace inside the batch workspace
   std::vector<Ctx> ctx_rel;                  // per network, ws relative to the batch workspace base
-  std::vector<BatchOp> tiny;                  // ordered by level, then network
-  std::vector<int32_t> seg;                  // [level][network] -> begin, end in `tiny`
-  std::vector<std::vector<std::vector<Op>>> big;   // [level][network] -> ops launched after the segment
+  std::vector<LevelOp> ops;                  // medium contractions
+  std::vector<LevelBlock> blocks;            // ordered by level
+  std::vector<uint32_t> level_block;         // per level: its first block; then the total
+  // [level][network] -> large ops, in the network's order
+  std::vector<std::vector<std::vector<Op>>> big;
   // leading small-contraction groups of all networks: blobs, workgroup table
   std::vector<char> blobs;
   std::vector<BatchGroup> groups;
   int64_t n_grouped = 0;                     // contractions in them
   uint32_t group_threads = 64, group_lds = 0;
   uint64_t blob_off = 0, group_off = 0;
-  uint64_t ctx_off = 0, ops_off = 0, seg_off = 0, ptr_off = 0, ws_bytes = 0;
+  uint64_t ctx_off = 0, ops_off = 0, blocks_off = 0, ptr_off = 0, ws_bytes = 0;
   int ptr_stride = 0;                        // pointer-table slots per network
   int64_t n_launches = 0;
   // prepared workspaces: graph per workspace address, at most kMaxGraphs
@@ -298,19 +366,28 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
   tn_batch_s* b = new tn_batch_s();
   b->prec = prec;
   b->n_nets = n_plans;
-  // per network: the mode-0 program cut into (segment, following large ops) levels
-  std::vector<std::vector<std::vector<BatchOp>>> segs(n_plans);
-  std::vector<std::vector<std::vector<Op>>> bigs(n_plans);
-  for (int j = 0; j < n_plans; j++) {
+  // per network: the mode-0 program's leading groups, then levels
+  const int N = n_plans;
+  const int eb = prec == TN_C128 ? 16 : 8;
+  std::vector<std::vector<uint32_t>> medium;               // [level] -> indices into b->ops
+  for (int j = 0; j < N; j++) {
     tn_plan_s* p = plans[j];
     std::lock_guard<std::mutex> lk(p->mu);
-    std::vector<Op> prog = forward_program(p, 0);
-    segs[j].emplace_back();
-    bigs[j].emplace_back();
+    const std::vector<Op> prog = forward_program(p, 0);
     bool leading = true;
-    for (const Op& op : prog) {
+    std::vector<std::pair<ArenaUse, int>> done;             // earlier ops and their levels
+    auto at_level = [&](int l) {
+      if ((int)medium.size() <= l) {
+        medium.resize((size_t)l + 1);
+        b->big.resize((size_t)l + 1, std::vector<std::vector<Op>>(N));
+      }
+    };
+    for (size_t i = 0; i < prog.size(); i++) {
+      const Op& op = prog[i];
       if (op.kind == OpKind::Counter || op.kind == OpKind::Fill) continue;
-      if (op.kind == OpKind::Tiny && leading) {
+      // groups that read no arena value depend on nothing; the next stage of a
+      // set that was cut reads theirs and is launched as a large op
+      if (op.kind == OpKind::Tiny && leading && op.tiny->reads.empty()) {
         for (uint32_t g = 0; g < op.tiny->n_groups; g++) b->groups.push_back({(uint32_t)j, g, b->blobs.size()});
         b->blobs.insert(b->blobs.end(), op.tiny->blob.begin(), op.tiny->blob.end());
         b->blobs.resize((b->blobs.size() + 63) / 64 * 64, 0);
@@ -320,39 +397,51 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
         continue;
       }
       leading = false;
-      BatchOp t;
-      if (as_tiny(op, prec, t)) {
-        if (!bigs[j].back().empty()) {   // a tiny op after large ones starts the next level
-          segs[j].emplace_back();
-          bigs[j].emplace_back();
-        }
-        segs[j].back().push_back(t);
-      } else {
-        bigs[j].back().push_back(op);
+      ArenaUse use = arena_use(op, eb);
+      const bool reduced = i + 1 < prog.size() && prog[i + 1].kind == OpKind::RowReduce;
+      if (reduced) {                                        // a split row op and its reduce pass: one unit
+        const ArenaUse r = arena_use(prog[i + 1], eb);
+        use.reads.insert(use.reads.end(), r.reads.begin(), r.reads.end());
+        use.writes.insert(use.writes.end(), r.writes.begin(), r.writes.end());
       }
+      int level = 0;
+      for (auto& d : done)
+        if (d.first.conflicts(use)) level = std::max(level, d.second + 1);
+      at_level(level);
+      LevelOp t;
+      if (as_level(op, prec, t)) {
+        t.net = (uint32_t)j;
+        medium[(size_t)level].push_back((uint32_t)b->ops.size());
+        b->ops.push_back(t);
+      } else {
+        b->big[(size_t)level][(size_t)j].push_back(op);
+        if (reduced) b->big[(size_t)level][(size_t)j].push_back(prog[i + 1]);
+      }
+      done.push_back({use, level});
+      if (reduced) i++;
     }
-    b->n_levels = std::max(b->n_levels, (int)segs[j].size());
     b->n_leaves.push_back(p->n_leaves);
     b->ptr_stride = std::max(b->ptr_stride, p->n_leaves + 2);
   }
-  const int L = b->n_levels, N = n_plans;
-  b->seg.assign((size_t)L * N * 2, 0);
-  b->big.assign(L, std::vector<std::vector<Op>>(N));
-  for (int l = 0; l < L; l++)
-    for (int j = 0; j < N; j++) {
-      b->seg[((size_t)l * N + j) * 2] = (int32_t)b->tiny.size();
-      if (l < (int)segs[j].size()) {
-        b->tiny.insert(b->tiny.end(), segs[j][l].begin(), segs[j][l].end());
-        b->big[l][j] = bigs[j][l];
-      }
-      b->seg[((size_t)l * N + j) * 2 + 1] = (int32_t)b->tiny.size();
+  b->n_levels = (int)medium.size();
+  for (auto& lvl : medium) {
+    b->level_block.push_back((uint32_t)b->blocks.size());
+    // longest sums first: they end last
+    std::stable_sort(lvl.begin(), lvl.end(), [&](uint32_t x, uint32_t y) { return b->ops[x].n_k > b->ops[y].n_k; });
+    for (uint32_t o : lvl) {
+      const LevelOp& t = b->ops[o];
+      const int per = t.mode == kPerThread ? 8 : (t.mode == kPerWave ? 2 : 0);   // log2 outputs per workgroup
+      const uint32_t n = t.n_out > per ? 1u << (t.n_out - per) : 1u;
+      for (uint32_t k = 0; k < n; k++) b->blocks.push_back({o, k});
     }
-  // workspace: contexts | tiny ops | segments | pointer tables | per-network plan workspaces
+  }
+  b->level_block.push_back((uint32_t)b->blocks.size());
+  // workspace: contexts | medium contractions | their blocks | pointer tables | per-network plan workspaces
   auto up = [](uint64_t x) { return (x + 255) / 256 * 256; };
   b->ctx_off = 0;
   b->ops_off = up(b->ctx_off + sizeof(Ctx) * (uint64_t)N);
-  b->seg_off = up(b->ops_off + sizeof(BatchOp) * (uint64_t)std::max<size_t>(b->tiny.size(), 1));
-  b->ptr_off = up(b->seg_off + sizeof(int32_t) * (uint64_t)b->seg.size());
+  b->blocks_off = up(b->ops_off + sizeof(LevelOp) * (uint64_t)b->ops.size());
+  b->ptr_off = up(b->blocks_off + sizeof(LevelBlock) * (uint64_t)b->blocks.size());
   b->blob_off = up(b->ptr_off + 8 * (uint64_t)b->ptr_stride * N);
   b->group_off = up(b->blob_off + b->blobs.size());
   for (BatchGroup& g : b->groups) g.blob += b->blob_off;
@@ -367,9 +456,9 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
   }
   b->ws_bytes = off;
   int64_t launches = b->groups.empty() ? 0 : 1;
-  for (int l = 0; l < L; l++) {
-    launches += 1;
-    for (int j = 0; j < N; j++) launches += (int64_t)b->big[l][j].size();
+  for (int l = 0; l < b->n_levels; l++) {
+    launches += b->level_block[(size_t)l] < b->level_block[(size_t)l + 1];
+    for (int j = 0; j < N; j++) launches += (int64_t)b->big[(size_t)l][(size_t)j].size();
   }
   b->n_launches = launches;
   *batch = b;
@@ -382,7 +471,7 @@ extern "C" int tn_batch_info(tn_batch_t b, uint64_t* workspace_bytes, int32_t* n
   std::lock_guard<std::mutex> lk(b->mu);
   if (workspace_bytes) *workspace_bytes = b->ws_bytes;
   if (n_levels) *n_levels = b->n_levels;
-  if (n_tiny) *n_tiny = b->n_grouped + (int64_t)b->tiny.size();
+  if (n_tiny) *n_tiny = b->n_grouped + (int64_t)b->ops.size();
   if (n_launches) *n_launches = b->n_launches;
   return TN_OK;
 }
@@ -405,9 +494,10 @@ extern "C" int tn_batch_prepare(tn_batch_t b, void* workspace, uint64_t workspac
   std::vector<Ctx> ctxs;
   for (int j = 0; j < b->n_nets; j++) ctxs.push_back(batch_ctx(b, j, base));
   BATCH_TRY(hipMemcpyAsync(w + b->ctx_off, ctxs.data(), sizeof(Ctx) * ctxs.size(), hipMemcpyHostToDevice, s));
-  if (!b->tiny.empty())
-    BATCH_TRY(hipMemcpyAsync(w + b->ops_off, b->tiny.data(), sizeof(BatchOp) * b->tiny.size(), hipMemcpyHostToDevice, s));
-  BATCH_TRY(hipMemcpyAsync(w + b->seg_off, b->seg.data(), sizeof(int32_t) * b->seg.size(), hipMemcpyHostToDevice, s));
+  if (!b->ops.empty()) {
+    BATCH_TRY(hipMemcpyAsync(w + b->ops_off, b->ops.data(), sizeof(LevelOp) * b->ops.size(), hipMemcpyHostToDevice, s));
+    BATCH_TRY(hipMemcpyAsync(w + b->blocks_off, b->blocks.data(), sizeof(LevelBlock) * b->blocks.size(), hipMemcpyHostToDevice, s));
+  }
   if (!b->groups.empty()) {
     BATCH_TRY(hipMemcpyAsync(w + b->blob_off, b->blobs.data(), b->blobs.size(), hipMemcpyHostToDevice, s));
     BATCH_TRY(hipMemcpyAsync(w + b->group_off, b->groups.data(), sizeof(BatchGroup) * b->groups.size(), hipMemcpyHostToDevice, s));
@@ -430,8 +520,8 @@ extern "C" int tn_batch_prepare(tn_batch_t b, void* workspace, uint64_t workspac
     batch_drop(lru->second);
     b->graphs.erase(lru);
   }
-  // capture: level by level, the interpreter launch, then the large ops of
-  // the networks on kBranches parallel branches (networks are independent;
+  // capture: the groups, then level by level the medium contractions' launch
+  // beside the large ops on parallel branches (a level's ops are independent;
   // the graph may run the branches concurrently), joined before the next level
   hipStream_t cs[kBranches] = {};
   hipEvent_t fork[kBranches] = {}, join[kBranches] = {};
@@ -453,21 +543,32 @@ extern "C" int tn_batch_prepare(tn_batch_t b, void* workspace, uint64_t workspac
   }
   for (int l = 0; l < b->n_levels && e == hipSuccess; l++) {
     CMEM const Ctx* dctx = reinterpret_cast<CMEM const Ctx*>(base + b->ctx_off);
-    CMEM const BatchOp* dops = reinterpret_cast<CMEM const BatchOp*>(base + b->ops_off);
-    CMEM const int32_t* dseg = reinterpret_cast<CMEM const int32_t*>(base + b->seg_off + sizeof(int32_t) * 2 * (uint64_t)l * N);
-    if (b->prec == TN_C128) hipLaunchKernelGGL(tiny_kernel<double>, dim3(N), dim3(kTinyThreads), 0, cs[0], dctx, dops, dseg);
-    else hipLaunchKernelGGL(tiny_kernel<float>, dim3(N), dim3(kTinyThreads), 0, cs[0], dctx, dops, dseg);
-    e = hipGetLastError();
-    for (int i = 1; i < kBranches && e == hipSuccess; i++) {
+    CMEM const LevelOp* dops = reinterpret_cast<CMEM const LevelOp*>(base + b->ops_off);
+    const uint32_t first = b->level_block[(size_t)l], n = b->level_block[(size_t)l + 1] - first;
+    CMEM const LevelBlock* dblk = reinterpret_cast<CMEM const LevelBlock*>(base + b->blocks_off) + first;
+    bool large = false;
+    for (int j = 0; j < N; j++) large = large || !b->big[(size_t)l][(size_t)j].empty();
+    // the large ones on the other branches, beside the medium ones' launch
+    for (int i = 1; i < kBranches && e == hipSuccess && large; i++) {
       e = hipEventRecord(fork[i], cs[0]);
       if (e == hipSuccess) e = hipStreamWaitEvent(cs[i], fork[i], 0);
     }
-    for (int j = 0; j < N && e == hipSuccess; j++)
+    if (n > 0 && e == hipSuccess) {
+      if (b->prec == TN_C128) hipLaunchKernelGGL(level_kernel<double>, dim3(n), dim3(kLevelThreads), 0, cs[0], dctx, dops, dblk);
+      else hipLaunchKernelGGL(level_kernel<float>, dim3(n), dim3(kLevelThreads), 0, cs[0], dctx, dops, dblk);
+      e = hipGetLastError();
+    }
+    int at = 0;
+    for (int j = 0; j < N && e == hipSuccess; j++) {
+      if (b->big[(size_t)l][(size_t)j].empty()) continue;
+      hipStream_t branch = cs[n > 0 ? 1 + at % (kBranches - 1) : at % kBranches];
+      at++;
       for (const Op& op : b->big[(size_t)l][(size_t)j]) {
-        e = launch_op(b->prec, ctxs[(size_t)j], op, cs[j % kBranches]);
+        e = launch_op(b->prec, ctxs[(size_t)j], op, branch);
         if (e != hipSuccess) break;
       }
-    for (int i = 1; i < kBranches && e == hipSuccess; i++) {
+    }
+    for (int i = 1; i < kBranches && e == hipSuccess && large; i++) {
       e = hipEventRecord(join[i], cs[i]);
       if (e == hipSuccess) e = hipStreamWaitEvent(cs[0], join[i], 0);
     }

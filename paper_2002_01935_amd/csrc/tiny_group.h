@@ -109,11 +109,13 @@ inline int thread_bits(const Item& it) {
 
 }  // namespace tiny_detail
 
-// Buffers an op reads and writes (buffer ids).
+// Buffers an op reads and writes (buffer ids).  A split row op counts as
+// writing C too, so that C never shares memory with its operands: a batch runs
+// the op and its reduce pass as one contraction.
 template <typename F>
 static void op_refs(Op& op, F&& f) {
   switch (op.kind) {
-    case OpKind::Row: f(op.row.a, false); f(op.row.b, false); if (op.row.k_split_bits > 0) f(op.row.part, true); else f(op.row.c, true); break;
+    case OpKind::Row: f(op.row.a, false); f(op.row.b, false); if (op.row.k_split_bits > 0) f(op.row.part, true); f(op.row.c, true); break;
     case OpKind::RowReduce: f(op.row.part, false); f(op.row.c, true); break;
     case OpKind::Gemm: f(op.gemm.a, false); f(op.gemm.b, false); if (op.gemm.k_split_bits > 0) f(op.gemm.part, true); f(op.gemm.c, true); break;
     case OpKind::Accum: f(op.accum.src, false); break;

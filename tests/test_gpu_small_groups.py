@@ -88,3 +88,30 @@ def test_small_groups(oracle_lib, name, prec):
         assert any(n["kernel"] == "tiny_tree_kernel" for n in plan.nodes()), name
     if name in ("pair-10-3", "pair-11-1"):
         assert plan.nodes()[0]["kernel"] != "tiny_tree_kernel", name
+
+
+@pytest.mark.parametrize("prec", ["c64_4m", "c128"])
+def test_batch_levels(oracle_lib, prec):
+    """A batch whose networks need several stages of groups (a chain longer
+    than one group), and contractions of every way the batch's level kernel
+    shares a sum: one thread, one wavefront or one workgroup per output."""
+    import torch
+
+    from paper_2002_01935_amd.binding import Batch, Plan
+    rng = np.random.default_rng(7)
+    nets = [_chain(400, rng)] + [_pair_tail(o, k, rng) for o, k in ((13, 0), (14, 2), (10, 5), (12, 6), (13, 8), (14, 7),
+                                                                    (2, 9), (8, 12), (4, 15), (9, 12), (1, 6))]
+    nets += [_chain(200, rng)] + [_random(s)[:2] + ([],) for s in range(3)]
+    plans = [Plan(net, tree, precision=prec) for net, tree, _ in nets]
+    batch = Batch(plans)
+    ws = batch.workspace()
+    batch.prepare(ws)
+    leaves = [to_dev(net, prec) for net, _, _ in nets]
+    tol = TOL_C128 if prec == "c128" else TOL_C64
+    refs = [oracle_lib.contract(net if prec == "c128" else c64_leaves(net), tree) for net, tree, _ in nets]
+    for _ in range(3):                                     # replays, with the workspace's old values in place
+        outs = batch.contract(leaves, ws)
+        torch.cuda.synchronize()
+        errs = [rel(o.cpu().numpy(), r) for o, r in zip(outs, refs)]
+        note("batch levels", prec, batch.info(), ["%.1e" % e for e in errs])
+        assert max(errs) < tol
