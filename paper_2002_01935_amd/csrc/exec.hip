@@ -153,15 +153,32 @@ extern "C" int tn_plan_info(tn_plan_t p, int32_t* W, int32_t* W_s, double* log2_
 
 // Tile variant of every matrix-core contraction of a program: the pinned
 // variant where it applies, else the autotuned one of its shape, else the
-// direct-to-LDS variant where the operands allow it (4M at three waves per
-// SIMD, 3M with 64 x 64 waves, BF16x3 on pre-split operands 256 x 128), else
-// the register-staged 128 x 128 tile.
+// default: the direct-to-LDS variant where the operands allow it (3M with
+// 64 x 64 waves, BF16x3 on pre-split operands 256 x 128), else the
+// register-staged tile.  4M, with `blocks` = 128 x 128 tiles of a launch (us or
+// ms per call, tile 9 / 14 / 15):
+//   fewer than one block per compute unit: 64 x 64 tiles.  2^8 x 2^13 x 2^7
+//     67 / 65 / 45 us, 2^10 x 2^11 x 2^9 200 / 166 / 112;
+//   from 2^9 summed values per block on: the prefetching ring (14).  2^11 x
+//     2^11 x 2^9 178 / 167 / 174 us, 2^10 x 2^10 x 2^16 4.20 / 4.04 / 4.53 ms,
+//     2^12 x 2^13 x 2^13 16.06 / 15.92 / 17.29;
+//   shorter sums: three waves per SIMD (9), whose blocks overlap their
+//     prologues better.  2^13 x 2^13 x 2^8 1.10 / 1.11 / 1.16 ms.
+// Register-staged: 64 x 64 below 512 blocks (2^11 x 2^11 x 2^9 190 against
+// 206 us; at twice the blocks 335 against 317).  Each pair of variants sums in
+// the same order.
 static std::array<int, 6> tile_key(const GemmOp& g, int prec) {
   return {g.n_h, g.n_m, g.n_n, g.n_k, g.k_split_bits, gemm_tile_ok(g, 7, prec) ? 1 : 0};
 }
 
-static int default_tile(const GemmOp& g, int prec) {
-  if (prec == TN_C64_4M && gemm_tile_ok(g, 9, prec)) return 9;
+static int default_tile(const GemmOp& g, int prec, int n_batch) {
+  if (prec == TN_C64_4M) {
+    const int tiles = std::max(0, g.n_m - 7) + std::max(0, g.n_n - 7) + g.n_h + std::max(0, g.k_split_bits);
+    const int64_t blocks = tiles < 32 ? int64_t(n_batch) << tiles : INT64_MAX;
+    const bool long_sum = g.n_k - std::max(0, g.k_split_bits) >= 9;
+    if (gemm_tile_ok(g, 9, prec)) return blocks < (long_sum ? 256 : 512) ? kSmallTileDl : (long_sum ? 14 : 9);
+    return blocks < 512 ? kSmallTile : 0;
+  }
   if (prec == TN_C64_3M && gemm_tile_ok(g, 7, prec)) return 7;
   if (g.ab_split && gemm_tile_ok(g, kSplitTile + 1, prec)) return kSplitTile + 1;
   return g.ab_split ? kSplitTile : 0;
@@ -171,7 +188,7 @@ static void assign_tiles(tn_plan_s* p, std::vector<Op>& prog) {
   for (Op& op : prog) {
     if (op.kind != OpKind::Gemm) continue;
     GemmOp& g = op.gemm;
-    int t = default_tile(g, p->prec);
+    int t = default_tile(g, p->prec, p->n_batch);
     auto it = p->tile_choice.find(tile_key(g, p->prec));
     if (p->pinned_tile >= 0 && gemm_tile_ok(g, p->pinned_tile, p->prec)) t = p->pinned_tile;
     else if (it != p->tile_choice.end()) t = it->second;
@@ -870,7 +887,7 @@ extern "C" int tn_plan_tune(tn_plan_t p, void* workspace, uint64_t workspace_byt
     }
     float best_ms = 1e30f, default_ms = 1e30f;
     int best_tile = 0;
-    const int dflt = default_tile(g, p->prec);
+    const int dflt = default_tile(g, p->prec, p->n_batch);
     for (size_t c = 0; c < cand.size(); c++) {
       std::array<float, kReps> v = t_ms[c];
       std::sort(v.begin(), v.end());

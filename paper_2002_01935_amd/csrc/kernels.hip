@@ -1853,6 +1853,8 @@ int gemm_tile_bits(int tile, int* bm, int* bn) {
     case 12: *bm = 7; *bn = 7; return 0;    // 128 x 128 BF16x3 on pre-split operands, 3 stages in flight
     case 13: *bm = 8; *bn = 7; return 0;    // 256 x 128 BF16x3 on pre-split operands, next stage's fragments prefetched
     case 14: *bm = 7; *bn = 7; return 0;    // 128 x 128 direct-to-LDS 4M, 4-stage ring, next stage's fragments prefetched
+    case kSmallTileDl: *bm = 6; *bn = 6; return 0;   // 64 x 64 direct-to-LDS 4M, 4 waves of 32 x 32
+    case kSmallTile: *bm = 6; *bn = 6; return 0;     // 64 x 64 register-staged 4M, 4 waves of 32 x 32
     default: return -1;
   }
 }
@@ -1867,7 +1869,7 @@ bool gemm_tile_ok(const GemmOp& op, int tile, int prec) {
   if (prec == TN_C128) return tile == kValuTile;
   if (tile < kNumTilesShared || tile == kValuTile) return true;
   if (prec == TN_C64_3M ? (tile != 7 && tile != 8 && tile != 9) : prec != TN_C64_4M) return false;
-  if (tile >= 7) {
+  if (tile >= 7 && tile != kSmallTile) {
     // the summed bits must be the lowest positions of both operands, in order
     if (op.n_k < 3) return false;
     for (int i = 0; i < op.n_k; i++)
@@ -1923,6 +1925,8 @@ const char* gemm_kernel_name(const GemmOp& op, int prec) {
     case 8: return "gemm_mfma_4m_dl<256,128,4,2>";
     case 9: return "gemm_mfma_4m_dl<128,128,2,2,3>";
     case 14: return "gemm_mfma_4m_dlp<128,128,2,2,2>";
+    case kSmallTileDl: return "gemm_mfma_4m_dl<64,64,2,2,4>";
+    case kSmallTile: return "gemm_mfma_4m<64,64,2,2>";
     default: return "?";
   }
 }
@@ -2038,6 +2042,8 @@ static hipError_t launch_gemm_kernel(const Ctx& ctx, const GemmOp& op, int prec,
     case 8: hipLaunchKernelGGL((gemm_mfma_4m_dl<256, 128, 4, 2>), grid, dim3(512), 0, s, ctx, op); break;
     case 9: hipLaunchKernelGGL((gemm_mfma_4m_dl<128, 128, 2, 2, 3>), grid, dim3(256), 0, s, ctx, op); break;
     case 14: hipLaunchKernelGGL((gemm_mfma_4m_dlp<128, 128, 2, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;
+    case kSmallTileDl: hipLaunchKernelGGL((gemm_mfma_4m_dl<64, 64, 2, 2, 4>), grid, dim3(256), 0, s, ctx, op); break;
+    case kSmallTile: hipLaunchKernelGGL((gemm_mfma_4m<64, 64, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

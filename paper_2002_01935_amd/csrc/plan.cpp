@@ -468,10 +468,13 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
       const int acc = std::min(std::min(k - kMaxSplitSumBits, 10), k - 1 - std::min(fa, fb));
       ks = std::max(ks, acc);
     }
-    // complex128: 64 x 64 tiles and about 7 us of FP64 matrix-core work per
-    // 2^6 summed values, so shorter parts pay; the partial buffer stays at
-    // most as large as the larger operand
-    if (p->prec == TN_C128 && p->split_f64) {
+    // shapes with few tiles are split further, for parallelism alone, where the
+    // order of the sum is free (complex128, and the reverse program, whose
+    // complex64 results are gradients; complex64 forward values keep the sums
+    // they had): 64 x 64 tiles fill the chip with 2^9 blocks, each summing at
+    // least 2^6 values (about 7 us of FP64 matrix-core work, 3.5 us in FP32);
+    // the partial buffer stays at most as large as the larger operand
+    if (p->prec == TN_C128 ? p->split_f64 : p->reverse) {
       const int tiles64 = std::max(0, fa - 6) + std::max(0, fb - 6) + h;
       ks = std::max(ks, std::min(std::min(k - 6, 9 - tiles64), std::max(h + fa + k, h + fb + k) - (h + fa + fb)));
       ks = std::min(ks, 10);
@@ -506,7 +509,9 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     // and how the sum is split follows from the rows of that choice ...
     const int most = std::min(fb, kMaxInThread), rows_most = h + fa + fb - most;
     const bool splitk = rows_most < 14 && k >= 6;
-    const int ks = splitk ? std::min(k - 6, std::max(0, 15 - rows_most)) : 0;
+    // (the reverse program: about 2^12 wavefronts, whose lane sums would cost
+    // more than their one step of products otherwise)
+    const int ks = splitk ? std::min(k - 6, std::max(0, (p->reverse ? 12 : 15) - rows_most)) : 0;
     // ... but with few rows fewer bits stay in-thread, so that the outputs
     // spread over the chip: a thread (a wavefront of split sums) with 16 of
     // them is a long serial chain next to idle compute units.  Every output
@@ -905,6 +910,11 @@ int build_backward(tn_plan_s* p, const std::vector<int32_t>& wrt, std::string& e
   for (size_t i = 0; i < large.size(); i++)
     if ((int)(i % stride) == stride - 1 || i + 1 == large.size()) ckpt[large[i]] = 1;
 
+  struct Reverse {
+    tn_plan_s* p;
+    explicit Reverse(tn_plan_s* q) : p(q) { p->reverse = true; }
+    ~Reverse() { p->reverse = false; }
+  } reverse(p);
   Prog prog;
   prog.ops.reserve((size_t)4 * n);
   std::vector<int> vbuf(nn, -1);   // current buffer holding the node value

@@ -88,6 +88,7 @@ struct tn_plan_s {
   // that run the program op by op on the host
   bool group_small = false;
   bool split_f64 = true;   // complex128 GEMMs split over K for parallelism alone
+  bool reverse = false;    // building the reverse program
 
   // bit expansion
   std::vector<int> bit_base, bit_count;   // per index
