@@ -248,7 +248,7 @@ static const char* op_kernel_name(const tn_plan_s* p, const Op& op, int* tile) {
   *tile = -1;
   switch (op.kind) {
     case OpKind::Row: {
-      if (op.row.k_split_bits >= 0) return "splitk_kernel";
+      if (op.row.k_split_bits >= 0) return op.row.rows_in_wave ? "splitk_rows_kernel" : "splitk_kernel";
       RowOp r = op.row;
       prepare_row(r);
       return row_stream_ok(r) ? "row_stream_kernel" : "row_kernel";

@@ -1743,6 +1743,19 @@ static void launch_row_u(bool splitk, dim3 grid, const Ctx& ctx, const RowOp& op
 }
 
 template <typename T, int NIN>
+static hipError_t launch_splitk_rows(const Ctx& ctx, const RowOp& op, hipStream_t s) {
+  dim3 grid(blocks_for(uint64_t(1) << op.k_split_bits, kRowThreads / 64), ctx.n_batch);
+  constexpr int kMost = sizeof(T) == 4 ? 32 : 16;
+  if (op.n_rows == 1 && 2 * NIN <= kMost) hipLaunchKernelGGL((splitk_rows_kernel<T, NIN, 2>), grid, dim3(kRowThreads), 0, s, ctx, op);
+  else if (op.n_rows == 2 && 4 * NIN <= kMost) hipLaunchKernelGGL((splitk_rows_kernel<T, NIN, 4>), grid, dim3(kRowThreads), 0, s, ctx, op);
+  else if constexpr (8 * NIN <= kMost) {
+    if (op.n_rows != 3) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((splitk_rows_kernel<T, NIN, 8>), grid, dim3(kRowThreads), 0, s, ctx, op);
+  } else return hipErrorInvalidValue;
+  return hipGetLastError();
+}
+
+template <typename T, int NIN>
 static void launch_row_stream_n(const Ctx& ctx, const RowOp& op, hipStream_t s) {
   const RowKOffsets ko = row_k_offsets(op);
   const bool contiguous = op.stage_c && sizeof(T) == 4 && NIN >= 2;
@@ -1804,6 +1817,15 @@ static hipError_t launch_row_t(const Ctx& ctx, const RowOp& op, hipStream_t s) {
     ubits = op.pair_a ? op.n_k - 1 : op.n_k;                 // (paired) k steps per thread
   }
   if (ubits < 0) return hipErrorInvalidValue;
+  if (splitk && op.rows_in_wave) {
+    if (op.k_split_bits < 1 || ubits < 1 || op.run_b.n != 0) return hipErrorInvalidValue;
+    switch (op.n_in) {
+      case 0: return launch_splitk_rows<T, 1>(ctx, op, s);
+      case 1: return launch_splitk_rows<T, 2>(ctx, op, s);
+      case 2: return launch_splitk_rows<T, 4>(ctx, op, s);
+      default: return hipErrorInvalidValue;
+    }
+  }
   dim3 grid(blocks_for(units, splitk ? kRowThreads / 64 : kRowThreads), ctx.n_batch);
   switch (op.n_in) {
     case 0: launch_row_u<T, 1>(splitk, grid, ctx, op, ubits, s); break;

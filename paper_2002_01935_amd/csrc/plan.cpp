@@ -394,6 +394,32 @@ static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool sp
   return std::max(0, std::min(most, outs - 16));
 }
 
+// Order of the summed bits of a split-K op (lanes take the lowest six, a
+// wavefront's steps the next).  Where the operands hold them in the same
+// order, that order: 64 consecutive k are a run of both.  Otherwise (leaves
+// with other axis orders, cotangents) the lanes take the three lowest of A and
+// fill up with the lowest of B, so that both are read in runs of 64 bytes
+// instead of A in one run and B an element per cache line; the steps go on with
+// the next of either.  Returns whether the order changed.
+static bool order_split_sum(std::vector<int>& K, const Layout& A, const Layout& B) {
+  std::vector<int> byB = K;
+  std::sort(byB.begin(), byB.end(), [&](int x, int y) { return B.pos_of(x) < B.pos_of(y); });
+  if (byB == K) return false;                           // K is in A's order
+  std::vector<int> out;
+  auto take = [&](const std::vector<int>& from) {
+    for (int b : from)
+      if (!contains(out, b)) { out.push_back(b); return; }
+  };
+  for (int i = 0; i < 3; i++) take(K);
+  for (int i = 0; i < 3; i++) take(byB);
+  while (out.size() < K.size()) {
+    take(K);
+    take(byB);
+  }
+  K.swap(out);
+  return true;
+}
+
 static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0, int conj_a,
                         int conj_b, const Ref& cref, const Layout& Cl, bool accumulate,
                         int forced_swap, int node, Prog& prog) {
@@ -511,12 +537,19 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     const bool splitk = rows_most < 14 && k >= 6;
     // (the reverse program: about 2^12 wavefronts, whose lane sums would cost
     // more than their one step of products otherwise)
-    const int ks = splitk ? std::min(k - 6, std::max(0, (p->reverse ? 12 : 15) - rows_most)) : 0;
+    int ks = splitk ? std::min(k - 6, std::max(0, (p->reverse ? 12 : 15) - rows_most)) : 0;
+    // summed bits in another order in B (the sum's order is then new anyway)
+    // and few rows, none of B's: one wavefront takes all rows, 2^10 to 2^12 of
+    // them, with up to 32 complex sums per lane in FP32, 16 in FP64
+    const bool scattered = splitk && order_split_sum(K, A.lay, B.lay);
+    const bool narrow = scattered && h == 0 && fa >= 1 && fa <= 3 && fb <= 2 &&
+                        fa + fb <= (p->elem_bytes == 8 ? 5 : 4) && k >= 17;
+    if (narrow) ks = std::min(k - 7, 12);
     // ... but with few rows fewer bits stay in-thread, so that the outputs
     // spread over the chip: a thread (a wavefront of split sums) with 16 of
     // them is a long serial chain next to idle compute units.  Every output
     // keeps its order of summation.
-    const int nin = in_thread_bits(h, fa, fb, k, accumulate, splitk, ks);
+    const int nin = narrow ? fb : in_thread_bits(h, fa, fb, k, accumulate, splitk, ks);
     std::vector<int> rows = H;
     rows.insert(rows.end(), FA.begin(), FA.end());
     rows.insert(rows.end(), FB.begin() + nin, FB.end());
@@ -545,6 +578,7 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     const int nrows = r.n_rows;
     if (splitk) {
       r.k_split_bits = ks;
+      r.rows_in_wave = narrow ? 1 : 0;
       op.grid_rows = int64_t(1) << (nrows + ks);
       if (ks > 0) {
         int pb = prog.new_buf((int64_t)p->elem_bytes << (nrows + nin + ks));

@@ -637,6 +637,95 @@ __global__ __launch_bounds__(kRowThreads) void splitk_kernel(Ctx ctx, RowOp op) 
   }
 }
 
+// wave_sum of V values (a power of two up to 64) at once: every step adds the
+// same pairs of lanes, but a lane keeps half of the values it still holds and
+// hands the other half to its partner, 63 exchanges for 64 values instead of
+// 384.  The sum of value i ends in the lanes whose top log2 V bits are i.
+template <typename T, int V>
+__device__ __forceinline__ T wave_sums(T (&v)[V], int lane) {
+  int n = V;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    if (n > 1) {
+      n >>= 1;
+      const bool up = (lane & o) != 0;
+#pragma unroll
+      for (int i = 0; i < V / 2; i++)
+        if (i < n) {
+          const T keep = up ? v[i + n] : v[i], send = up ? v[i] : v[i + n];
+          v[i] = keep + __shfl_xor(send, o, 64);
+        }
+    } else {
+      v[0] += __shfl_xor(v[0], o, 64);
+    }
+  }
+  return v[0];
+}
+
+// splitk_kernel with all R = 2^n_rows rows in one wavefront, for rows that B
+// does not have: B is loaded once instead of once per row (from the L2 of
+// another XCD as often as not).  Bound by the reads of A and B.  For operands
+// that hold the summed bits in different orders; 2^3 rows x 2^2 values x 2^22
+// (402 MB) 252 -> 132 us, 2^1 x 1 x 2^24 457 -> 124 us per call.
+template <typename T, int NIN, int R>
+__global__ __launch_bounds__(kRowThreads) void splitk_rows_kernel(Ctx ctx, RowOp op) {
+  using V = typename C2<T>::t;
+  constexpr int U = 2;
+  const int z = blockIdx.y;
+  const int64_t sid = slice_id(ctx, z);
+  if (sid < 0) return;
+  const int lane = threadIdx.x & 63;
+  const uint64_t wave = uint64_t(blockIdx.x) * (blockDim.x / 64) + (threadIdx.x >> 6);
+  const int ks = op.k_split_bits;
+  if (wave >> ks) return;
+  const uint32_t chunk = (uint32_t)wave;
+  const int eb = sizeof(V);
+  GMEM const V* A = reinterpret_cast<GMEM const V*>(resolve(ctx, op.a, z, sid, eb));
+  GMEM const V* B = reinterpret_cast<GMEM const V*>(resolve(ctx, op.b, z, sid, eb));
+  const int cbits = op.n_k - ks;                  // >= 7
+  const uint32_t ba = deposit_runs32(chunk, op.run_ka_chunk) + deposit_runs32(lane, op.run_ka_lane);
+  const uint32_t bb = deposit_runs32(chunk, op.run_kb_chunk) + deposit_runs32(lane, op.run_kb_lane);
+  uint32_t inb[NIN], ina[R];
+#pragma unroll
+  for (int j = 0; j < NIN; j++) inb[j] = op.in_off_b[j];
+#pragma unroll
+  for (int r = 0; r < R; r++) ina[r] = deposit_runs32((uint32_t)r, op.run_a);
+  T sum[2 * R * NIN];                             // (row, in-thread output, re / im)
+#pragma unroll
+  for (int i = 0; i < 2 * R * NIN; i++) sum[i] = 0;
+  const uint32_t steps = 1u << (cbits - 6);
+  uint32_t xa = 0, xb = 0;
+  for (uint32_t i = 0; i < steps; i += U) {
+    V a[U][R], b[U][NIN];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+#pragma unroll
+      for (int r = 0; r < R; r++) a[u][r] = conjv(ld(A + ba + ina[r] + xa), op.conj_a);
+#pragma unroll
+      for (int j = 0; j < NIN; j++) b[u][j] = conjv(ld(B + bb + inb[j] + xb), op.conj_b);
+      const uint32_t c = u + 1 < U ? uint32_t(u) : i + u;
+      xa += kstep(op.kstep_a, c, cbits - 6);
+      xb += kstep(op.kstep_b, c, cbits - 6);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int j = 0; j < NIN; j++)
+#pragma unroll
+        for (int r = 0; r < R; r++) {
+          sum[2 * (r * NIN + j)] += a[u][r].x * b[u][j].x - a[u][r].y * b[u][j].y;
+          sum[2 * (r * NIN + j) + 1] += a[u][r].x * b[u][j].y + a[u][r].y * b[u][j].x;
+        }
+  }
+  constexpr int N2 = 2 * R * NIN;                 // one lane of each group of 64 / N2 stores its part of an output
+  const T total = wave_sums<T, N2>(sum, lane);
+  if (lane & (64 / N2 - 1)) return;
+  // partials [row][in][chunk], as splitk_kernel's
+  const uint32_t at = (uint32_t)lane / (64 / N2);
+  GMEM T* P = reinterpret_cast<GMEM T*>(resolve(ctx, op.part, z, sid, eb));
+  P[2 * ((uint64_t(at >> 1) << ks) + chunk) + (at & 1)] = total;
+}
+
 // Sum of the split-K partials of each output in a fixed order: one wavefront
 // per output, lane l adds chunks l, l + 64, ... (contiguous in the partials
 // buffer), then the fixed butterfly of wave_sum.  Deterministic.
@@ -653,6 +742,8 @@ __global__ __launch_bounds__(kRowThreads) void reduce_kernel(Ctx ctx, RowOp op) 
   GMEM const V* P = reinterpret_cast<GMEM const V*>(resolve(ctx, op.part, z, sid, eb)) + (o << op.k_split_bits);
   const uint32_t nch = 1u << op.k_split_bits;
   T sx = 0, sy = 0;
+  // (unrolled: the loads of eight steps in flight, added in order)
+#pragma unroll 8
   for (uint32_t ch = lane; ch < nch; ch += 64) {
     const V p = ld(P + ch);
     sx += p.x;
