@@ -232,9 +232,11 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
   } else {
     return false;
   }
-  // short sums by one thread; long ones shared, by a wavefront while there
-  // are outputs enough for a few thousand of them
-  t.mode = t.n_k < 6 || t.n_out >= 14 ? kPerThread : (t.n_k >= 12 && t.n_out <= 8 ? kPerGroup : kPerWave);
+  // Short sums by one thread (a step of four values takes about 1 us of load
+  // latency), long ones shared by a wavefront; with 2^14 outputs a wavefront
+  // per output pays from 2^8 values on, with 2^16 the threads fill the chip.
+  const bool per_thread = t.n_k < 6 || t.n_out >= 16 || (t.n_out >= 14 && t.n_k < 8);
+  t.mode = per_thread ? kPerThread : (t.n_k >= 12 && t.n_out <= 8 ? kPerGroup : kPerWave);
   return true;
 }
 

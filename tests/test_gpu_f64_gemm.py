@@ -1,5 +1,5 @@
 """complex128 GEMMs on the FP64 matrix cores (gemm_mfma_f64) against the
-oracle: partial and full tiles of both block shapes, batch bits, shuffled
+oracle: partial and full tiles of the three block shapes, batch bits, shuffled
 operand and output orders, few and many summed values, sums split over the
 grid, and conjugated operands (reverse mode)."""
 
@@ -14,10 +14,11 @@ pytestmark = pytest.mark.gpu
 TWO = Tree(np.array([0], np.int32), np.array([1], np.int32))
 
 # (h, m, n, k), kernel, split over K; the oracle's work stays under 2^27 products
-SHAPES = [((0, 5, 5, 4), "64,64", False), ((0, 5, 9, 5), "64,64", False), ((2, 6, 7, 4), "64,64", False),
-          ((0, 7, 6, 8), "64,64", True), ((1, 6, 6, 11), "64,64", True), ((0, 8, 5, 10), "64,64", True),
-          ((3, 5, 6, 9), "64,64", True), ((0, 11, 11, 4), "128,64", False), ((4, 9, 9, 4), "128,64", False),
-          ((0, 12, 10, 5), "128,64", False)]
+SHAPES = [((0, 5, 5, 4), "32,64", False), ((0, 5, 9, 5), "32,64", False), ((2, 6, 7, 4), "32,64", False),
+          ((0, 7, 6, 8), "32,64", True), ((1, 6, 6, 11), "32,64", True), ((0, 8, 5, 10), "32,64", True),
+          ((3, 5, 6, 9), "32,64", True), ((0, 11, 11, 4), "128,64", False), ((4, 9, 9, 4), "128,64", False),
+          ((0, 12, 10, 5), "128,64", False), ((0, 10, 11, 4), "64,64", False), ((3, 9, 9, 5), "64,64", False),
+          ((0, 10, 10, 6), "32,64", False)]
 
 
 @pytest.mark.parametrize("shape,kernel,split", SHAPES, ids=["-".join(map(str, s[0])) for s in SHAPES])
