@@ -44,19 +44,29 @@ constexpr int kLevelThreads = 256;
 // (one per hardware queue a process gets by default)
 constexpr int kBranches = 4;
 
+// A position list as at most kLevelRuns runs (entries as in BitRuns).
+constexpr int kLevelRuns = 8;
+struct LevelList {
+  int32_t n;
+  uint32_t r[kLevelRuns];
+};
+
 // One medium contraction: for each of 2^n_out outputs,
 //   C[o] = sum over 2^n_k summed values of opA(A[o, k]) * opB(B[o, k])
-// (opX = complex conjugate when conj_x), or C[o] = A[o] without B.  Output bit
-// j sits at position oa[j] / ob[j] / oc[j] of A / B / C (-1: absent from that
-// operand), summed bit j at ka[j] / kb[j].
+// (opX = complex conjugate when conj_x), or C[o] = A[o] without B.  The lists
+// place o in A / B / C (oa, ob, oc), the threads of one output over its lowest
+// summed bits (ta, tb) and the summed values above those, two bits at first
+// (step_a, step_b: their offsets) and the rest (ha, hb).
 struct LevelOp {
   Ref a, b, c;
   uint32_t net;
   int32_t n_out, n_k, mode;
   int32_t has_b, conj_a, conj_b, pad;
-  int8_t oa[kLevelBits], ob[kLevelBits], oc[kLevelBits], ka[kLevelBits], kb[kLevelBits];
+  uint32_t step_a[2], step_b[2];
+  LevelList oa, ob, oc, ta, tb, ha, hb;
+  int32_t pad2;
 };
-static_assert(offsetof(LevelOp, oa) % 4 == 0 && sizeof(LevelOp) % 8 == 0, "LevelOp layout");
+static_assert(sizeof(LevelOp) % 8 == 0, "LevelOp layout");
 
 // A workgroup's contraction and its block of that contraction's outputs.
 struct LevelBlock {
@@ -67,42 +77,14 @@ struct LevelBlock {
 // the lowest six summed bits) or the whole workgroup (the lowest eight).
 enum { kPerThread = 0, kPerWave = 1, kPerGroup = 2 };
 
-// A list of up to 24 byte positions in registers (uniform: scalar loads).
-struct PosList {
-  uint64_t w[3];
-};
-__device__ __forceinline__ PosList pos_list(CMEM const int8_t* p) {
-  PosList l;
-#pragma unroll
-  for (int i = 0; i < 3; i++) {
-    CMEM const uint32_t* q = reinterpret_cast<CMEM const uint32_t*>(p) + 2 * i;
-    l.w[i] = q[0] | uint64_t(q[1]) << 32;
-  }
-  return l;
-}
-// The list from entry `first` on (first < 8 or a multiple of 8).
-__device__ __forceinline__ PosList tail(const PosList& l, int first) {
-  PosList r;
-  const int s = 8 * (first & 7);
-  r.w[0] = first >= 8 ? l.w[1] : l.w[0];
-  r.w[1] = first >= 8 ? l.w[2] : l.w[1];
-  r.w[2] = first >= 8 ? 0 : l.w[2];
-  if (s) {
-    r.w[0] = (r.w[0] >> s) | (r.w[1] << (64 - s));
-    r.w[1] = (r.w[1] >> s) | (r.w[2] << (64 - s));
-    r.w[2] >>= s;
-  }
-  return r;
-}
-// Offset of the low n bits of v (positions < 0: absent).
-__device__ __forceinline__ uint32_t place(uint32_t v, PosList l, int n) {
+// Offset of v through a list (uniform: scalar loads, a uniform branch per run).
+__device__ __forceinline__ uint32_t place(uint32_t v, const LevelList& l) {
   uint32_t off = 0;
-#pragma unroll 1
-  for (int i = 0; i < n; i++) {
-    const int p = (int8_t)l.w[0];
-    off |= p >= 0 ? (v & 1u) << p : 0u;
-    v >>= 1;
-    l = tail(l, 1);
+#pragma unroll
+  for (int i = 0; i < kLevelRuns; i++) {
+    if (i >= l.n) break;
+    const uint32_t w = l.r[i];
+    off |= ((v >> (w & 0xFF)) & (~0u >> (32 - (w >> 16)))) << ((w >> 8) & 0xFF);
   }
   return off;
 }
@@ -129,26 +111,22 @@ __global__ __launch_bounds__(kLevelThreads) void level_kernel(CMEM const Ctx* ct
   const uint32_t o = (e.block * kLevelThreads + tid) >> ts, q = tid & ((1u << ts) - 1u);
   const bool active = (o >> n_out) == 0;
   const uint32_t oo = active ? o : 0u;
-  const PosList ka = pos_list(op->ka), kb = pos_list(op->kb);
   V acc;
   acc.x = 0;
   acc.y = 0;
   if (!has_b) {
-    acc = ld(A + place(oo, pos_list(op->oa), n_out));
+    acc = ld(A + place(oo, cload(&op->oa)));
   } else {
     const T ca = op->conj_a ? T(-1) : T(1), cb = op->conj_b ? T(-1) : T(1);
-    GMEM const V* Ao = A + place(oo, pos_list(op->oa), n_out) + place(q, ka, ts);
-    GMEM const V* Bo = B + place(oo, pos_list(op->ob), n_out) + place(q, kb, ts);
+    GMEM const V* Ao = A + place(oo, cload(&op->oa)) + place(q, cload(&op->ta));
+    GMEM const V* Bo = B + place(oo, cload(&op->ob)) + place(q, cload(&op->tb));
     // the remaining summed bits in order, four values at a time (uniform offsets)
-    const PosList wa = tail(ka, ts), wb = tail(kb, ts);
-    const int walk = n_k - ts;
-    const int lo = walk < 2 ? walk : 2;
-    const uint32_t a0 = walk >= 1 ? 1u << (wa.w[0] & 31) : 0u, b0 = walk >= 1 ? 1u << (wb.w[0] & 31) : 0u;
-    const uint32_t a1 = walk >= 2 ? 1u << ((wa.w[0] >> 8) & 31) : 0u, b1 = walk >= 2 ? 1u << ((wb.w[0] >> 8) & 31) : 0u;
-    const PosList ha = tail(wa, lo), hb = tail(wb, lo);
+    const int walk = n_k - ts, lo = walk < 2 ? walk : 2;
+    const uint32_t a0 = op->step_a[0], b0 = op->step_b[0], a1 = op->step_a[1], b1 = op->step_b[1];
+    const LevelList ha = cload(&op->ha), hb = cload(&op->hb);
     const uint32_t steps = 1u << (walk - lo);
     for (uint32_t s = 0; s < steps; s++) {
-      const uint32_t xa = place(s, ha, walk - lo), xb = place(s, hb, walk - lo);
+      const uint32_t xa = place(s, ha), xb = place(s, hb);
       V a[4], b[4];
       a[0] = ld(Ao + xa); b[0] = ld(Bo + xb);
       a[1] = ld(Ao + xa + a0); b[1] = ld(Bo + xb + b0);
@@ -176,7 +154,7 @@ __global__ __launch_bounds__(kLevelThreads) void level_kernel(CMEM const Ctx* ct
       }
     }
   }
-  if (active && q == 0) st(C + place(o, pos_list(op->oc), n_out), acc);
+  if (active && q == 0) st(C + place(o, cload(&op->oc)), acc);
 }
 
 // The small-contraction launches that begin each network's program, all in one
@@ -194,10 +172,21 @@ __global__ __launch_bounds__(512) void tiny_batch_kernel(uint64_t base, CMEM con
   tiny_group<T>(ctx, base + e.blob, (int)e.group, 0, 0, smem);
 }
 
+// Runs of n entries of a position list; false when there are too many.
+static bool level_runs(const int8_t* pos, int n, LevelList& l) {
+  BitRuns R;
+  make_runs(pos, n, R);
+  l.n = R.n;
+  if (R.n > kLevelRuns) return false;
+  for (int i = 0; i < R.n; i++) l.r[i] = R.r[i];
+  return true;
+}
+
 // Whether op is a medium contraction, and its descriptor if so.
 static bool as_level(const Op& op, int prec, LevelOp& t) {
   std::memset(&t, 0, sizeof t);
-  for (int j = 0; j < kLevelBits; j++) t.oa[j] = t.ob[j] = t.oc[j] = t.ka[j] = t.kb[j] = -1;
+  int8_t oa[kLevelBits], ob[kLevelBits], oc[kLevelBits], ka[kLevelBits], kb[kLevelBits];
+  for (int j = 0; j < kLevelBits; j++) oa[j] = ob[j] = oc[j] = ka[j] = kb[j] = -1;
   auto fits = [&](int n_out, int n_k) {
     t.n_out = n_out;
     t.n_k = n_k;
@@ -206,9 +195,9 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
   if (op.kind == OpKind::Row) {
     const RowOp& r = op.row;
     if (r.accumulate || !fits(r.n_rows + r.n_in, r.n_k)) return false;
-    for (int j = 0; j < r.n_rows; j++) { t.oa[j] = r.row_a[j]; t.ob[j] = r.row_b[j]; t.oc[j] = r.row_c[j]; }
-    for (int j = 0; j < r.n_in; j++) { t.ob[r.n_rows + j] = r.in_b[j]; t.oc[r.n_rows + j] = r.in_c[j]; }
-    for (int j = 0; j < r.n_k; j++) { t.ka[j] = r.k_a[j]; t.kb[j] = r.k_b[j]; }
+    for (int j = 0; j < r.n_rows; j++) { oa[j] = r.row_a[j]; ob[j] = r.row_b[j]; oc[j] = r.row_c[j]; }
+    for (int j = 0; j < r.n_in; j++) { ob[r.n_rows + j] = r.in_b[j]; oc[r.n_rows + j] = r.in_c[j]; }
+    for (int j = 0; j < r.n_k; j++) { ka[j] = r.k_a[j]; kb[j] = r.k_b[j]; }
     t.a = r.a; t.b = r.b; t.c = r.c;
     t.has_b = 1;
     t.conj_a = r.conj_a; t.conj_b = r.conj_b;
@@ -216,10 +205,10 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
     const GemmOp& g = op.gemm;
     if (g.accumulate || g.ab_split || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
     int j = 0;
-    for (int i = 0; i < g.n_h; i++, j++) { t.oa[j] = g.a_h[i]; t.ob[j] = g.b_h[i]; t.oc[j] = g.c_h[i]; }
-    for (int i = 0; i < g.n_m; i++, j++) { t.oa[j] = g.a_m[i]; t.oc[j] = g.c_m[i]; }
-    for (int i = 0; i < g.n_n; i++, j++) { t.ob[j] = g.b_n[i]; t.oc[j] = g.c_n[i]; }
-    for (int i = 0; i < g.n_k; i++) { t.ka[i] = g.a_k[i]; t.kb[i] = g.b_k[i]; }
+    for (int i = 0; i < g.n_h; i++, j++) { oa[j] = g.a_h[i]; ob[j] = g.b_h[i]; oc[j] = g.c_h[i]; }
+    for (int i = 0; i < g.n_m; i++, j++) { oa[j] = g.a_m[i]; oc[j] = g.c_m[i]; }
+    for (int i = 0; i < g.n_n; i++, j++) { ob[j] = g.b_n[i]; oc[j] = g.c_n[i]; }
+    for (int i = 0; i < g.n_k; i++) { ka[i] = g.a_k[i]; kb[i] = g.b_k[i]; }
     t.a = g.a; t.b = g.b; t.c = g.c;
     t.has_b = 1;
     t.conj_a = g.conj_a; t.conj_b = g.conj_b;
@@ -227,7 +216,7 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
     const PermuteOp& pm = op.perm;
     const int c128 = prec == TN_C128;
     if (pm.accumulate || !fits(pm.n_bits, 0) || pm.src_c128 != c128 || pm.dst_c128 != c128 || pm.per_slice_serial) return false;
-    for (int j = 0; j < pm.n_bits; j++) { t.oa[j] = pm.src_pos[j]; t.oc[j] = pm.dst_pos[j]; }
+    for (int j = 0; j < pm.n_bits; j++) { oa[j] = pm.src_pos[j]; oc[j] = pm.dst_pos[j]; }
     t.a = pm.src; t.c = pm.dst;
   } else {
     return false;
@@ -237,7 +226,14 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
   // per output pays from 2^8 values on, with 2^16 the threads fill the chip.
   const bool per_thread = t.n_k < 6 || t.n_out >= 16 || (t.n_out >= 14 && t.n_k < 8);
   t.mode = per_thread ? kPerThread : (t.n_k >= 12 && t.n_out <= 8 ? kPerGroup : kPerWave);
-  return true;
+  const int ts = t.mode == kPerThread ? 0 : (t.mode == kPerWave ? 6 : 8), lo = std::min(2, t.n_k - ts);
+  for (int i = 0; i < lo; i++) {
+    t.step_a[i] = 1u << ka[ts + i];
+    t.step_b[i] = 1u << kb[ts + i];
+  }
+  return level_runs(oa, t.n_out, t.oa) && level_runs(ob, t.n_out, t.ob) && level_runs(oc, t.n_out, t.oc) &&
+         level_runs(ka, ts, t.ta) && level_runs(kb, ts, t.tb) && level_runs(ka + ts + lo, t.n_k - ts - lo, t.ha) &&
+         level_runs(kb + ts + lo, t.n_k - ts - lo, t.hb);
 }
 
 // Arena bytes an op reads and writes (elements of eb bytes; operands there are
