@@ -380,7 +380,7 @@ static Op split_op(const Ref& src, const int8_t* fpos, int nf, const int8_t* hpo
 
 // In-thread free bits of a row op with batch, row-side and in-thread-side bits
 // h, fa, fb and k summed bits (sum split in 2^ks chunks, one wavefront per row
-// and chunk, when `splitk`).  All that fit up to 2^14 rows (2^13 wavefronts);
+// and chunk, when `splitk`).  All that fit from 2^16 rows (2^13 wavefronts) on;
 // below, as few as bring the rows to 2^16 threads (one per SIMD lane of the
 // chip), or the wavefronts to 2^12.  A small tensor applied to every row keeps
 // them all: its streaming kernel needs B to have no row bit.  Measured: launches
@@ -389,7 +389,7 @@ static Op split_op(const Ref& src, const int8_t* fpos, int nf, const int8_t* hpo
 static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool splitk, int ks) {
   const int most = std::min(fb, kMaxInThread), outs = h + fa + fb, rows = outs - most;
   if (splitk) return rows + ks >= 13 ? most : std::max(0, std::min(most, outs + ks - 12));
-  if (rows >= 14) return most;
+  if (rows >= 16) return most;
   if (!accumulate && h == 0 && fb == most && rows >= 6 && k <= 2 && most + k <= 4) return most;
   return std::max(0, std::min(most, outs - 16));
 }
