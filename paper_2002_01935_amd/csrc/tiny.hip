@@ -28,7 +28,7 @@ struct alignas(16) TinyArg {
 };
 
 // One workgroup per group and in-flight slice.  Bound by latency: a chain of
-// launch, table and operand loads, then ~0.4 us per level of the group (LDS
+// launch, table and operand loads, then about 1 us per level of the group (LDS
 // reads and a barrier), against 4.4 us and more per contraction as launches of
 // their own (95 % of a circuit's contractions, in trees 10 to 15 levels deep).
 // Whole calls on MI355X, before and after: 122 contractions of a 3 x 3 circuit
