@@ -666,7 +666,7 @@ __device__ __forceinline__ T wave_sums(T (&v)[V], int lane) {
 // does not have: B is loaded once instead of once per row (from the L2 of
 // another XCD as often as not).  Bound by the reads of A and B.  For operands
 // that hold the summed bits in different orders; 2^3 rows x 2^2 values x 2^22
-// (402 MB) 252 -> 132 us, 2^1 x 1 x 2^24 457 -> 124 us per call.
+// (402 MB) 291 -> 145 us per call, 2^1 x 1 x 2^24 457 -> 119.
 template <typename T, int NIN, int R>
 __global__ __launch_bounds__(kRowThreads) void splitk_rows_kernel(Ctx ctx, RowOp op) {
   using V = typename C2<T>::t;
