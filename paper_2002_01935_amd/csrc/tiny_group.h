@@ -286,18 +286,51 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
     }
     if (fits) break;
   }
+  const int G = (int)members.size();
+  auto at_end = [&](int i) {                             // copy of a leaf's cotangent into its gradient
+    const Op& o = prog.ops[i];
+    return o.kind == OpKind::Permute && o.perm.accumulate && o.perm.per_slice_serial && o.perm.n_bits <= kTinyTensorBits;
+  };
+  // Order of the other ops: the program's, except that an op which reads a
+  // group's result comes after all ops that the group waits for.  A group of a
+  // reverse program can hold a forward value that an early op reads and, up
+  // its connected set, a cotangent that needs a later op.  Groups and ops form
+  // no cycle (see `stage`), so a walk that visits inputs first finds the order.
+  std::vector<int> others;
+  {
+    std::vector<char> seen_unit((size_t)nops + G, 0);      // ops, then groups
+    std::vector<std::pair<int, bool>> todo;                // unit, inputs done
+    for (int i0 = 0; i0 < nops; i0++) {
+      if (small[i0] || dropped[i0] || at_end(i0)) continue;
+      todo.push_back({i0, false});
+      while (!todo.empty()) {
+        const auto [u, ready] = todo.back();
+        todo.pop_back();
+        if (ready) {
+          if (u < nops) others.push_back(u);
+          continue;
+        }
+        if (seen_unit[(size_t)u]) continue;
+        seen_unit[(size_t)u] = 1;
+        todo.push_back({u, true});
+        const size_t from = todo.size();
+        auto need = [&](int q) {
+          if (q < 0) return;
+          const int v = small[q] ? nops + item[q].group : q;
+          if (v != u && !seen_unit[(size_t)v]) todo.push_back({v, false});
+        };
+        if (u < nops) inputs(u, need);
+        else for (int i : members[(size_t)(u - nops)]) inputs(i, need);
+        std::stable_sort(todo.begin() + (int64_t)from, todo.end(), [](auto& x, auto& y) { return x.first > y.first; });
+      }
+    }
+  }
   // Launch positions in the sequence of the other ops (a group at position q
   // runs before the q-th of them): as soon as the external operands are
   // there, or at the end when nothing but gradient copies reads the results.
   std::vector<int> pos(nops, -1);
   int seq = 0;
-  auto at_end = [&](int i) {                             // copy of a leaf's cotangent into its gradient
-    const Op& o = prog.ops[i];
-    return o.kind == OpKind::Permute && o.perm.accumulate && o.perm.per_slice_serial && o.perm.n_bits <= kTinyTensorBits;
-  };
-  for (int i = 0; i < nops; i++)
-    if (!small[i] && !dropped[i] && !at_end(i)) pos[i] = seq++;
-  const int G = (int)members.size();
+  for (int i : others) pos[i] = seq++;
   std::vector<int> gpos(G, 0), order(G);
   std::vector<char> has_reader(G, 0);
   for (int g = 0; g < G; g++) {
@@ -473,8 +506,7 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
   auto launch_at = [&](int q) {
     for (auto it = launches.lower_bound({q, 0}); it != launches.end() && it->first.first == q; ++it) emit(it->second);
   };
-  for (int i = 0; i < nops; i++) {
-    if (pos[i] < 0) continue;
+  for (int i : others) {
     launch_at(pos[i]);
     out.ops.push_back(prog.ops[i]);
   }

@@ -1,0 +1,134 @@
+"""The planner's forward and reverse programs, with the small contractions
+collected into group launches, run op by op on the host
+(tests/emu/emu_program.cpp) against the oracle: every value is written before
+an op reads it and keeps its memory until its last reader, whatever the order
+of the launches."""
+
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from tn_inputs.graphs import random_network
+from tn_inputs.greedy import find_tree
+from tn_inputs.network import Network, Tree
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CLANG = "/opt/rocm/llvm/bin/clang++"
+PREC = {"c64_4m": 0, "c128": 3}
+# the arithmetic is in double, values are stored in the plan's type: products
+# of tens of float32 roundings (6e-8 each), or of double ones
+TOL = {"c64_4m": 1e-5, "c128": 1e-12}
+
+
+@pytest.fixture(scope="module")
+def emu(tmp_path_factory):
+    if not os.path.exists(CLANG) and shutil.which("clang++") is None:
+        pytest.skip("no clang++ for the host build")
+    cxx = CLANG if os.path.exists(CLANG) else shutil.which("clang++")
+    out = str(tmp_path_factory.mktemp("emu") / "emu_program")
+    csrc = os.path.join(ROOT, "paper_2002_01935_amd", "csrc")
+    subprocess.run([cxx, "-O2", "-std=c++20", "-I", csrc, "-I", os.path.join(ROOT, "include"),
+                    os.path.join(ROOT, "tests", "emu", "emu_program.cpp"), os.path.join(csrc, "plan.cpp"), "-o", out,
+                    "-lpthread"], check=True, capture_output=True)
+    return out
+
+
+def run(emu, d, net, tree, prec, wrt, go, sliced=(), ids=(0,), grouped=True):
+    lists = [[len(t) for t in net.leaf_idx], [i for t in net.leaf_idx for i in t], list(net.idx_dim), list(net.out_idx),
+             list(tree.left), list(tree.right), list(sliced), list(ids), list(wrt), [PREC[prec], 0, int(grouped)]]
+    with open(os.path.join(d, "net.txt"), "w") as f:
+        for x in lists:
+            f.write(" ".join(str(int(v)) for v in [len(x)] + x) + "\n")
+    with open(os.path.join(d, "in.bin"), "wb") as f:
+        for t in list(net.leaves) + [go]:
+            np.ascontiguousarray(t, dtype=np.complex128).tofile(f)
+    r = subprocess.run([emu, os.path.join(d, "net.txt"), os.path.join(d, "in.bin"), os.path.join(d, "out.bin")],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+    flat = np.fromfile(os.path.join(d, "out.bin"), dtype=np.complex128)
+    shapes = [tuple(net.idx_dim[e] for e in net.out_idx)] + [np.shape(net.leaves[v]) for v in wrt]
+    out, at = [], 0
+    for s in shapes:
+        n = int(np.prod(s, dtype=np.int64))
+        out.append(flat[at:at + n].reshape(s))
+        at += n
+    assert at == len(flat)
+    return out[0], out[1:]
+
+
+def check(emu, oracle_lib, tmp_path, net, tree, wrt, precs=PREC, sliced=(), ids=(0,), seed=0):
+    rng = np.random.default_rng(seed)
+    shape = tuple(net.idx_dim[e] for e in net.out_idx)
+    go = rng.normal(size=shape) + 1j * rng.normal(size=shape)
+    ref = oracle_lib.contract(net, tree, sliced=list(sliced), slice_ids=list(ids))
+    refs = oracle_lib.grad(net, tree, go, wrt, sliced=list(sliced), slice_ids=list(ids))
+    for prec in precs:
+        got, grads = run(emu, str(tmp_path), net, tree, prec, wrt, go, sliced, ids)
+        for g, r in zip([got] + grads, [ref] + refs):
+            assert np.linalg.norm(np.ravel(g) - np.ravel(r)) <= TOL[prec] * np.linalg.norm(np.ravel(r)), prec
+
+
+def forked_group():
+    """(((L1 L2) l2) l3) w) u with wrt = {3, 5}: in the reverse program one
+    connected set of small contractions holds both a forward value that a large
+    contraction reads and, further on, a cotangent that needs a later large one."""
+    a, m = list(range(11)), list(range(18, 30))
+    i1, i2, j1, j2, k1, k2, z = 11, 12, 13, 14, 15, 16, 17
+    idx = [a + [i1, i2], a + [j1, j2], [i1, k1], [i2, k2], [k1] + m, [k2, z]]
+    rng = np.random.default_rng(3)
+    leaves = [(rng.normal(size=(2,) * len(t)) + 1j * rng.normal(size=(2,) * len(t))) for t in idx]
+    net = Network(leaves, idx, [2] * 30, [j1, j2, z] + m)
+    net.check()
+    return net, Tree(np.array([0, 6, 7, 8, 9], np.int32), np.array([1, 2, 3, 4, 5], np.int32))
+
+
+# (leaves, largest rank, outputs, graph): random networks whose reverse
+# programs hold such a group, and others
+GRAPHS = [(21, 5, 5, 57), (16, 6, 4, 34881), (19, 5, 5, 99433), (24, 6, 6, 23629), (25, 4, 5, 51936), (36, 5, 6, 21123),
+          (14, 5, 3, 1), (22, 4, 4, 2), (30, 5, 3, 3), (40, 4, 2, 4)]
+
+
+def random_case(leaves, rank, n_out, graph):
+    net = random_network(leaves, 7 * leaves // 5, rank, graph, n_out=n_out, dims=(2, 4), hyper=True)
+    return net, find_tree(net, seed=0, trials=1)
+
+
+def test_reader_of_a_group_that_waits_for_a_later_op(emu, oracle_lib, tmp_path):
+    net, tree = forked_group()
+    check(emu, oracle_lib, tmp_path, net, tree, [3, 5])
+
+
+@pytest.mark.parametrize("case", GRAPHS)
+def test_random_programs(emu, oracle_lib, tmp_path, case):
+    net, tree = random_case(*case)
+    check(emu, oracle_lib, tmp_path, net, tree, list(range(net.n_leaves)))
+
+
+def test_random_program_sliced(emu, oracle_lib, tmp_path):
+    net, tree = random_case(*GRAPHS[0])
+    sliced = [e for e in range(net.n_idx) if e not in net.out_idx][:3]
+    check(emu, oracle_lib, tmp_path, net, tree, list(range(net.n_leaves)), sliced=sliced, ids=(0, 3, 5))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("prec", PREC)
+@pytest.mark.parametrize("case", [None] + GRAPHS[:6])
+def test_gradients_on_the_gpu(oracle_lib, case, prec):
+    import torch
+
+    from paper_2002_01935_amd.binding import Plan
+    from tests.gpu_util import TOL_C64, TOL_C128, note, ref_net, rel, to_dev
+    net, tree = forked_group() if case is None else random_case(*case)
+    wrt = [3, 5] if case is None else list(range(net.n_leaves))
+    rng = np.random.default_rng(0)
+    shape = tuple(net.idx_dim[e] for e in net.out_idx)
+    go = rng.normal(size=shape) + 1j * rng.normal(size=shape)
+    grads = Plan(net, tree, precision=prec).backward(to_dev(net, prec), torch.from_numpy(go), wrt)
+    torch.cuda.synchronize()
+    refs = oracle_lib.grad(ref_net(net, prec), tree, go, wrt)
+    worst = max(rel(g.cpu().numpy(), r) for g, r in zip(grads, refs))
+    note("gradients, program order", case, prec, "%.2e" % worst)
+    assert worst < (TOL_C128 if prec == "c128" else TOL_C64)
