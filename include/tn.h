@@ -320,10 +320,11 @@ int tn_contract_sliced_noalloc(tn_plan_t plan, const void* const* leaves, int64_
  * this time), so the plans may be destroyed afterwards.  The groups of small
  * contractions at the bottom of all networks run in one launch; the
  * contractions that remain are sorted into levels by their dependences, and
- * a level's contractions with at most 2^22 (outputs x summed values), of all
- * networks, run in one launch, the others with the ordinary kernels.
+ * a level's contractions with at most 2^22 (outputs x summed values) and at
+ * most 2^16 summed values, of all networks, run in one launch, the others with
+ * the ordinary kernels.
  * The result of network j is its tn_contract result, up to the rounding of
- * sums taken in another order.
+ * sums taken in another order: no value passes more additions than there.
  *
  * tn_batch_info: workspace bytes, number of levels, number of contractions
  * that run in the shared launches, and launches per call.

@@ -40,6 +40,15 @@ namespace tn {
 constexpr int kLevelBits = 24;      // bit-list capacity of a medium contraction
 constexpr int kLevelWorkBits = 22;  // log2 (outputs x summed values) of the largest one
 constexpr int kLevelThreads = 256;
+constexpr int kLongSum = 6;         // log2 summed values from which the planner splits a sum over lanes
+constexpr int kLevelStep = 3;       // log2 summed values of a thread's step
+constexpr int kLevelTree = 5;       // levels of a thread's addition tree above a step
+// log2 summed values of the longest contraction: 2^8 per thread of a
+// workgroup.  Above, the sum would be one compute unit's serial chain, and the
+// split-K kernels spread it over the chip: a batch of one 2^17 sum 47 us per
+// call by one workgroup, 35 by them; of 2^16, 40 and 35 (eight of them 40 and
+// 151), of eight 2^22 2494 and 429.
+constexpr int kLevelSumBits = kLevelStep + kLevelTree + 8;
 // parallel branches of a level's large contractions in the captured graph
 // (one per hardware queue a process gets by default)
 constexpr int kBranches = 4;
@@ -55,14 +64,14 @@ struct LevelList {
 //   C[o] = sum over 2^n_k summed values of opA(A[o, k]) * opB(B[o, k])
 // (opX = complex conjugate when conj_x), or C[o] = A[o] without B.  The lists
 // place o in A / B / C (oa, ob, oc), the threads of one output over its lowest
-// summed bits (ta, tb) and the summed values above those, two bits at first
+// summed bits (ta, tb) and the summed values above those, kLevelStep bits at first
 // (step_a, step_b: their offsets) and the rest (ha, hb).
 struct LevelOp {
   Ref a, b, c;
   uint32_t net;
   int32_t n_out, n_k, mode;
   int32_t has_b, conj_a, conj_b, pad;
-  uint32_t step_a[2], step_b[2];
+  uint32_t step_a[kLevelStep], step_b[kLevelStep];
   LevelList oa, ob, oc, ta, tb, ha, hb;
   int32_t pad2;
 };
@@ -87,6 +96,73 @@ __device__ __forceinline__ uint32_t place(uint32_t v, const LevelList& l) {
     off |= ((v >> (w & 0xFF)) & (~0u >> (32 - (w >> 16)))) << ((w >> 8) & 0xFF);
   }
   return off;
+}
+
+template <typename V>
+__device__ __forceinline__ V cadd(V a, V b) {
+  a.x += b.x;
+  a.y += b.y;
+  return a;
+}
+
+// One thread's 2^walk products, 2^LO per step (uniform offsets, their loads in
+// flight together).  SERIAL: added one after another, as the row kernel does.
+// Else as a balanced tree: sum[l] waits for its neighbour of 2^l steps.  With
+// the lanes and wavefronts a value then passes n_k additions, no more than in
+// the split-K kernels: 2^16 values per output in complex64 have an error of
+// 1.6e-7 (split-K kernels 2.4e-7, one running sum per thread 6.7e-7), at the
+// same time per call.
+template <typename T, int LO, bool SERIAL>
+__device__ __forceinline__ typename C2<T>::t thread_sum(GMEM const typename C2<T>::t* A, GMEM const typename C2<T>::t* B,
+                                                        CMEM const LevelOp* op, int walk, T ca, T cb) {
+  using V = typename C2<T>::t;
+  constexpr int N = 1 << LO;
+  const LevelList ha = cload(&op->ha), hb = cload(&op->hb);
+  uint32_t da[N], db[N];
+  da[0] = db[0] = 0;
+#pragma unroll
+  for (int l = 0; l < LO; l++)
+#pragma unroll
+    for (int i = 0; i < (1 << l); i++) {
+      da[(1 << l) + i] = da[i] + op->step_a[l];
+      db[(1 << l) + i] = db[i] + op->step_b[l];
+    }
+  V acc, sum[kLevelTree];
+  acc.x = 0;
+  acc.y = 0;
+  const uint32_t steps = 1u << (walk - LO);
+  for (uint32_t s = 0; s < steps; s++) {
+    const uint32_t xa = place(s, ha), xb = place(s, hb);
+    V a[N], b[N];
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      a[i] = ld(A + xa + da[i]);
+      b[i] = ld(B + xb + db[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+      a[i].y *= ca;
+      b[i].y *= cb;
+      if constexpr (SERIAL) acc = cfma(acc, a[i], b[i]);
+      else a[i] = cmul(a[i], b[i]);
+    }
+    if constexpr (!SERIAL) {
+#pragma unroll
+      for (int n = N / 2; n >= 1; n /= 2)
+#pragma unroll
+        for (int i = 0; i < n; i++) a[i] = cadd(a[i], a[i + n]);
+      acc = a[0];
+#pragma unroll
+      for (int l = 0; l < kLevelTree; l++) {
+        if (((s >> l) & 1u) == 0) {
+          sum[l] = acc;
+          break;
+        }
+        acc = cadd(sum[l], acc);
+      }
+    }
+  }
+  return acc;
 }
 
 // A level's medium contractions of all networks.  Latency bound (a few
@@ -120,38 +196,31 @@ __global__ __launch_bounds__(kLevelThreads) void level_kernel(CMEM const Ctx* ct
     const T ca = op->conj_a ? T(-1) : T(1), cb = op->conj_b ? T(-1) : T(1);
     GMEM const V* Ao = A + place(oo, cload(&op->oa)) + place(q, cload(&op->ta));
     GMEM const V* Bo = B + place(oo, cload(&op->ob)) + place(q, cload(&op->tb));
-    // the remaining summed bits in order, four values at a time (uniform offsets)
-    const int walk = n_k - ts, lo = walk < 2 ? walk : 2;
-    const uint32_t a0 = op->step_a[0], b0 = op->step_b[0], a1 = op->step_a[1], b1 = op->step_b[1];
-    const LevelList ha = cload(&op->ha), hb = cload(&op->hb);
-    const uint32_t steps = 1u << (walk - lo);
-    for (uint32_t s = 0; s < steps; s++) {
-      const uint32_t xa = place(s, ha), xb = place(s, hb);
-      V a[4], b[4];
-      a[0] = ld(Ao + xa); b[0] = ld(Bo + xb);
-      a[1] = ld(Ao + xa + a0); b[1] = ld(Bo + xb + b0);
-      a[2] = ld(Ao + xa + a1); b[2] = ld(Bo + xb + b1);
-      a[3] = ld(Ao + xa + a0 + a1); b[3] = ld(Bo + xb + b0 + b1);
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        a[u].y *= ca;
-        b[u].y *= cb;
-        if (u < 1 || (u < 2 && walk >= 1) || walk >= 2) acc = cfma(acc, a[u], b[u]);
+    const int walk = n_k - ts;
+    if (n_k < kLongSum) {
+      switch (walk) {
+        case 0: acc = thread_sum<T, 0, true>(Ao, Bo, op, walk, ca, cb); break;
+        case 1: acc = thread_sum<T, 1, true>(Ao, Bo, op, walk, ca, cb); break;
+        case 2: acc = thread_sum<T, 2, true>(Ao, Bo, op, walk, ca, cb); break;
+        default: acc = thread_sum<T, 3, true>(Ao, Bo, op, walk, ca, cb);
+      }
+    } else {
+      switch (walk) {
+        case 0: acc = thread_sum<T, 0, false>(Ao, Bo, op, walk, ca, cb); break;
+        case 1: acc = thread_sum<T, 1, false>(Ao, Bo, op, walk, ca, cb); break;
+        case 2: acc = thread_sum<T, 2, false>(Ao, Bo, op, walk, ca, cb); break;
+        default: acc = thread_sum<T, 3, false>(Ao, Bo, op, walk, ca, cb);
       }
     }
   }
-  if (mode != kPerThread) {                      // fixed order: butterfly, then the wavefronts in order
+  if (mode != kPerThread) {                      // fixed order: butterfly, then the four wavefronts
     acc.x = wave_sum(acc.x);
     acc.y = wave_sum(acc.y);
     if (mode == kPerGroup) {
       __shared__ V part[kLevelThreads / 64];
       if ((tid & 63) == 0) part[tid >> 6] = acc;
       __syncthreads();
-      acc = part[0];
-      for (int w = 1; w < kLevelThreads / 64; w++) {
-        acc.x += part[w].x;
-        acc.y += part[w].y;
-      }
+      acc = cadd(cadd(part[0], part[1]), cadd(part[2], part[3]));
     }
   }
   if (active && q == 0) st(C + place(o, cload(&op->oc)), acc);
@@ -190,7 +259,7 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
   auto fits = [&](int n_out, int n_k) {
     t.n_out = n_out;
     t.n_k = n_k;
-    return n_out <= kLevelBits && n_k <= kLevelBits && n_out + n_k <= kLevelWorkBits;
+    return n_out <= kLevelBits && n_k <= kLevelSumBits && n_out + n_k <= kLevelWorkBits;
   };
   if (op.kind == OpKind::Row) {
     const RowOp& r = op.row;
@@ -221,12 +290,13 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
   } else {
     return false;
   }
-  // Short sums by one thread (a step of four values takes about 1 us of load
-  // latency), long ones shared by a wavefront; with 2^14 outputs a wavefront
-  // per output pays from 2^8 values on, with 2^16 the threads fill the chip.
-  const bool per_thread = t.n_k < 6 || t.n_out >= 16 || (t.n_out >= 14 && t.n_k < 8);
+  // Short sums by one thread (a step takes about 1 us of load latency), long
+  // ones shared by a wavefront; with 2^14 outputs a wavefront per output pays
+  // from 2^8 values on, with 2^16 the threads fill the chip.
+  const bool per_thread = t.n_k < kLongSum || t.n_out >= 16 || (t.n_out >= 14 && t.n_k < 8);
   t.mode = per_thread ? kPerThread : (t.n_k >= 12 && t.n_out <= 8 ? kPerGroup : kPerWave);
-  const int ts = t.mode == kPerThread ? 0 : (t.mode == kPerWave ? 6 : 8), lo = std::min(2, t.n_k - ts);
+  const int ts = t.mode == kPerThread ? 0 : (t.mode == kPerWave ? 6 : 8), lo = std::min(kLevelStep, t.n_k - ts);
+  if (t.n_k - ts > kLevelStep + kLevelTree) return false;
   for (int i = 0; i < lo; i++) {
     t.step_a[i] = 1u << ka[ts + i];
     t.step_b[i] = 1u << kb[ts + i];
