@@ -322,7 +322,8 @@ int tn_contract_sliced_noalloc(tn_plan_t plan, const void* const* leaves, int64_
  * contractions that remain are sorted into levels by their dependences, and
  * a level's contractions with at most 2^22 (outputs x summed values) and at
  * most 2^16 summed values, of all networks, run in one launch, the others with
- * the ordinary kernels.
+ * the ordinary kernels (contractions that TN_FLAG_GEMM_ALL_SIZES asks to have
+ * on the matrix cores: from 2^17 outputs x summed values on).
  * The result of network j is its tn_contract result, up to the rounding of
  * sums taken in another order: no value passes more additions than there.
  *

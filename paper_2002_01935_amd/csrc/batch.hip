@@ -39,6 +39,9 @@ namespace tn {
 
 constexpr int kLevelBits = 24;      // bit-list capacity of a medium contraction
 constexpr int kLevelWorkBits = 22;  // log2 (outputs x summed values) of the largest one
+// GEMM-class ones are asked for by TN_FLAG_GEMM_ALL_SIZES (none is smaller than
+// 2^25 without it): larger ones run on the matrix cores, as the flag says
+constexpr int kLevelGemmBits = 16;
 constexpr int kLevelThreads = 256;
 constexpr int kLongSum = 6;         // log2 summed values from which the planner splits a sum over lanes
 constexpr int kLevelStep = 3;       // log2 summed values of a thread's step
@@ -272,7 +275,8 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
     t.conj_a = r.conj_a; t.conj_b = r.conj_b;
   } else if (op.kind == OpKind::Gemm) {
     const GemmOp& g = op.gemm;
-    if (g.accumulate || g.ab_split || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
+    if (g.accumulate || g.ab_split || g.k_split_bits > 0 || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
+    if (t.n_out + t.n_k > kLevelGemmBits) return false;
     int j = 0;
     for (int i = 0; i < g.n_h; i++, j++) { oa[j] = g.a_h[i]; ob[j] = g.b_h[i]; oc[j] = g.c_h[i]; }
     for (int i = 0; i < g.n_m; i++, j++) { oa[j] = g.a_m[i]; oc[j] = g.c_m[i]; }
