@@ -43,42 +43,23 @@ inline int rank_of(const Operand& o, int p) {
 
 // Fills `it` from a contraction op; false when the op is not a small one.
 // Without `splits`, contractions of the split-K kernel are left to it.
-inline bool describe(const Op& op, bool gemm_too, bool splits, Item& it) {
+inline bool describe(const Op& op, bool splits, Item& it) {
+  if (op.kind != OpKind::Row) return false;
+  const RowOp& r = op.row;
+  if (r.accumulate || (r.k_split_bits >= 0 && !splits)) return false;
+  const int n_out = r.n_rows + r.n_in, n_k = r.n_k;
+  if (n_out + n_k > kTinyWorkBits || n_out > kTinyTensorBits) return false;
+  if (r.c.kind != 1 || r.a.kind == 2 || r.b.kind == 2) return false;
   int8_t ca[kMaxBits], cb[kMaxBits], ka[kMaxBits], kb[kMaxBits];   // by position in C / summed bit
-  int n_out, n_k;
-  const Ref *ra, *rb, *rc;
-  if (op.kind == OpKind::Row) {
-    const RowOp& r = op.row;
-    if (r.accumulate || (r.k_split_bits >= 0 && !splits)) return false;
-    it.split = r.k_split_bits >= 0;
-    n_out = r.n_rows + r.n_in;
-    n_k = r.n_k;
-    if (n_out + n_k > kTinyWorkBits) return false;
-    for (int i = 0; i < r.n_rows; i++) { ca[r.row_c[i]] = r.row_a[i]; cb[r.row_c[i]] = r.row_b[i]; }
-    for (int i = 0; i < r.n_in; i++) { ca[r.in_c[i]] = -1; cb[r.in_c[i]] = r.in_b[i]; }
-    for (int i = 0; i < n_k; i++) { ka[i] = r.k_a[i]; kb[i] = r.k_b[i]; }
-    ra = &r.a; rb = &r.b; rc = &r.c;
-    it.conj = (r.conj_a ? 1 : 0) | (r.conj_b ? 2 : 0);
-  } else if (op.kind == OpKind::Gemm && gemm_too) {
-    const GemmOp& g = op.gemm;
-    if (g.accumulate || g.ab_split) return false;
-    n_out = g.n_h + g.n_m + g.n_n;
-    n_k = g.n_k;
-    if (n_out + n_k > kTinyWorkBits) return false;
-    for (int i = 0; i < g.n_h; i++) { ca[g.c_h[i]] = g.a_h[i]; cb[g.c_h[i]] = g.b_h[i]; }
-    for (int i = 0; i < g.n_m; i++) { ca[g.c_m[i]] = g.a_m[i]; cb[g.c_m[i]] = -1; }
-    for (int i = 0; i < g.n_n; i++) { ca[g.c_n[i]] = -1; cb[g.c_n[i]] = g.b_n[i]; }
-    for (int i = 0; i < n_k; i++) { ka[i] = g.a_k[i]; kb[i] = g.b_k[i]; }
-    ra = &g.a; rb = &g.b; rc = &g.c;
-    it.conj = (g.conj_a ? 1 : 0) | (g.conj_b ? 2 : 0);
-  } else {
-    return false;
-  }
-  if (rc->kind != 1 || ra->kind == 2 || rb->kind == 2 || n_out > kTinyTensorBits) return false;
-  auto operand = [&](const Ref& r, const int8_t* c, const int8_t* k, Operand& o, uint64_t& on, uint64_t& kn) {
-    o.leaf = r.kind == 0;
-    o.id = o.leaf ? r.slot : (int)r.off;
-    o.ref = r;
+  for (int i = 0; i < r.n_rows; i++) { ca[r.row_c[i]] = r.row_a[i]; cb[r.row_c[i]] = r.row_b[i]; }
+  for (int i = 0; i < r.n_in; i++) { ca[r.in_c[i]] = -1; cb[r.in_c[i]] = r.in_b[i]; }
+  for (int i = 0; i < n_k; i++) { ka[i] = r.k_a[i]; kb[i] = r.k_b[i]; }
+  it.split = r.k_split_bits >= 0;
+  it.conj = (r.conj_a ? 1 : 0) | (r.conj_b ? 2 : 0);
+  auto operand = [&](const Ref& ref, const int8_t* c, const int8_t* k, Operand& o, uint64_t& on, uint64_t& kn) {
+    o.leaf = ref.kind == 0;
+    o.id = o.leaf ? ref.slot : (int)ref.off;
+    o.ref = ref;
     int n = n_k;
     for (int i = 0; i < n_out; i++) n += c[i] >= 0;
     if (n > kTinyTensorBits) return false;
@@ -91,8 +72,8 @@ inline bool describe(const Op& op, bool gemm_too, bool splits, Item& it) {
   };
   it.n_out = n_out;
   it.n_k = n_k;
-  it.c = (int)rc->off;
-  return operand(*ra, ca, ka, it.a, it.oa, it.ka) && operand(*rb, cb, kb, it.b, it.ob, it.kb);
+  it.c = (int)r.c.off;
+  return operand(r.a, ca, ka, it.a, it.oa, it.ka) && operand(r.b, cb, kb, it.b, it.ob, it.kb);
 }
 
 // Threads per output (log2).  A sum that the row kernel would run in index
@@ -133,13 +114,12 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
   // complex64 forward values keep the rounding of the split-K kernel's
   // butterfly, so that sums over slices do not depend on the grouping
   const bool splits = p->prec == TN_C128 || root_buf < 0;
-  const bool gemm_too = !(p->opt.flags & TN_FLAG_GEMM_ALL_SIZES);
   const int nops = (int)prog.ops.size(), nbuf = (int)prog.bufs.size();
   std::vector<Item> item(nops);
   std::vector<char> small(nops, 0), dropped(nops, 0);
   for (int i = 0; i < nops; i++) {
     item[i].op = i;
-    small[i] = describe(prog.ops[i], gemm_too, splits, item[i]);
+    small[i] = describe(prog.ops[i], splits, item[i]);
   }
   std::vector<int> producer(nbuf, -1);                   // op that completes each buffer
   std::vector<std::vector<int>> readers(nbuf);
