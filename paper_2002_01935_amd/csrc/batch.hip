@@ -101,13 +101,6 @@ __device__ __forceinline__ uint32_t place(uint32_t v, const LevelList& l) {
   return off;
 }
 
-template <typename V>
-__device__ __forceinline__ V cadd(V a, V b) {
-  a.x += b.x;
-  a.y += b.y;
-  return a;
-}
-
 // One thread's 2^walk products, 2^LO per step (uniform offsets, their loads in
 // flight together).  SERIAL: added one after another, as the row kernel does.
 // Else as a balanced tree: sum[l] waits for its neighbour of 2^l steps.  With

@@ -60,6 +60,13 @@ __device__ __forceinline__ V cmul(V a, V b) {
 }
 
 template <typename V>
+__device__ __forceinline__ V cadd(V a, V b) {
+  a.x += b.x;
+  a.y += b.y;
+  return a;
+}
+
+template <typename V>
 __device__ __forceinline__ V cfma(V acc, V a, V b) {
   acc.x = acc.x + a.x * b.x - a.y * b.y;
   acc.y = acc.y + a.x * b.y + a.y * b.x;

@@ -78,8 +78,9 @@ inline bool describe(const Op& op, bool splits, Item& it) {
 
 // Threads per output (log2).  A sum that the row kernel would run in index
 // order stays one thread's (at most 32 values unless rows are many): grouping
-// does not change its rounding.  The longer sums of the split-K kernel are
-// shared by threads of one wavefront, about four values each.
+// does not change its rounding.  The longer sums of the split-K kernel (at most
+// 2^10 values, operands being that small) are shared by threads of one
+// wavefront, 2^2 to 2^4 values each.
 inline int split_bits(const Item& it) {
   if (!it.split) return 0;
   return std::max(0, std::min(std::min(it.n_k - 2, 6), kTinyMaxThreadBits - it.n_out));

@@ -23,6 +23,18 @@ __device__ __forceinline__ V lane_xor(V v, int m) {
   return v;
 }
 
+// cfma with its four roundings spelled out, as the row kernel's code has them:
+// left to the compiler, products shared with the other branch below would be
+// rounded before they are added.
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+template <typename V>
+__device__ __forceinline__ V cfma_in_order(V acc, V a, V b) {
+  acc.x = fused(-a.y, b.y, fused(a.x, b.x, acc.x));
+  acc.y = fused(a.y, b.x, fused(a.x, b.y, acc.y));
+  return acc;
+}
+
 // Group g of the blob at `blob`, for in-flight slice z.
 template <typename T>
 __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g, int z, int64_t sid, char* smem) {
@@ -96,9 +108,9 @@ __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g,
       const bool active = found && (o >> n_out) == 0;
       const V* A = data + a_lds + nibbles(o, oa, n_out) + nibbles(q, ka >> (4 * kk), ks);
       const V* B = data + b_lds + nibbles(o, ob, n_out) + nibbles(q, kb >> (4 * kk), ks);
-      V acc;
-      acc.x = 0;
-      acc.y = 0;
+      V acc, half, quarter;
+      acc.x = half.x = quarter.x = 0;
+      acc.y = half.y = quarter.y = 0;
       if (active) {
         // four summed values at a time: their loads are independent
         const uint32_t a0 = kk >= 1 ? 1u << (ka & 15) : 0u, b0 = kk >= 1 ? 1u << (kb & 15) : 0u;
@@ -114,7 +126,24 @@ __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g,
           for (int u = 0; u < 4; u++) {
             a[u].y *= ca;
             b[u].y *= cb;
-            if (u < 1 || (u < 2 && kk >= 1) || kk >= 2) acc = cfma(acc, a[u], b[u]);
+          }
+          if (ks == 0) {
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+              if (u < 1 || (u < 2 && kk >= 1) || kk >= 2) acc = cfma_in_order(acc, a[u], b[u]);
+          } else {
+            // a shared sum, 2^2 to 2^4 values per thread: a balanced tree over
+            // them and the lanes, as many additions per value (n_k) as in the
+            // split-K kernel that runs it alone
+            acc = cadd(cadd(cmul(a[0], b[0]), cmul(a[1], b[1])), cadd(cmul(a[2], b[2]), cmul(a[3], b[3])));
+            const uint32_t step = j >> 2;
+            if ((step & 1u) == 0) {
+              half = acc;
+            } else {
+              acc = cadd(half, acc);
+              if ((step & 2u) == 0) quarter = acc;
+              else acc = cadd(quarter, acc);
+            }
           }
         }
       }
