@@ -394,6 +394,13 @@ static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool sp
   return std::max(0, std::min(most, outs - 16));
 }
 
+// Most additions that a value of a split-K op passes, one after another: a
+// lane's 2^(k - 6 - ks) values, the 2^ks chunks in the reduce pass (64 lanes,
+// then their butterfly).  The rounding error grows as its root.
+static int64_t split_chain(int k, int ks) {
+  return (int64_t(1) << (k - 6 - ks)) + (ks > 6 ? (int64_t(1) << (ks - 6)) + 6 : ks);
+}
+
 // Order of the summed bits of a split-K op (lanes take the lowest six, a
 // wavefront's steps the next).  Where the operands hold them in the same
 // order, that order: 64 consecutive k are a run of both.  Otherwise (leaves
@@ -535,9 +542,10 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     // and how the sum is split follows from the rows of that choice ...
     const int most = std::min(fb, kMaxInThread), rows_most = h + fa + fb - most;
     const bool splitk = rows_most < 14 && k >= 6;
-    // (the reverse program: about 2^12 wavefronts, whose lane sums would cost
-    // more than their one step of products otherwise)
-    int ks = splitk ? std::min(k - 6, std::max(0, (p->reverse ? 12 : 15) - rows_most)) : 0;
+    // (2^15 wavefronts; the reverse program: about 2^12, whose lane sums would
+    // cost more than their one step of products otherwise)
+    const int ks_most = splitk ? std::min(k - 6, std::max(0, 15 - rows_most)) : 0;
+    int ks = splitk && p->reverse ? std::min(k - 6, std::max(0, 12 - rows_most)) : ks_most;
     // summed bits in another order in B (the sum's order is then new anyway)
     // and few rows, none of B's: one wavefront takes all rows, 2^10 or 2^11 of
     // them (2^12: 166 us per call instead of 145 on 2^3 x 2^2 x 2^22), with up to 32 complex sums per lane in FP32, 16 in FP64
@@ -545,6 +553,8 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     const bool narrow = scattered && h == 0 && fa >= 1 && fa <= 3 && fb <= 2 &&
                         fa + fb <= (p->elem_bytes == 8 ? 5 : 4) && k >= 17;
     if (narrow) ks = std::min(k - 7, 11);
+    // fewer chunks only where no value passes more additions for it
+    while (splitk && ks < ks_most && split_chain(k, ks) > split_chain(k, ks_most)) ks++;
     // ... but with few rows fewer bits stay in-thread, so that the outputs
     // spread over the chip: a thread (a wavefront of split sums) with 16 of
     // them is a long serial chain next to idle compute units.  Every output

@@ -284,7 +284,7 @@ int main(int argc, char** argv) {
   p.sliced = list<int64_t>(f);
   const std::vector<int64_t> ids = list<int64_t>(f);
   const std::vector<int32_t> wrt = list<int32_t>(f);
-  const std::vector<int32_t> opt = list<int32_t>(f);       // precision, flags, group_small
+  const std::vector<int32_t> opt = list<int32_t>(f);       // precision, flags, group_small[, list split contractions only]
   fclose(f);
   const int nl = p.n_leaves = (int)p.rank.size();
   p.n_idx = (int)p.idx_dim.size();
@@ -299,6 +299,13 @@ int main(int argc, char** argv) {
   if (build_plan(&p, err) || (!wrt.empty() && build_backward(&p, wrt, err))) {
     fprintf(stderr, "plan: %s\n", err.c_str());
     return 2;
+  }
+  if (opt.size() > 3) {                                    // split contractions: reverse, rows, in-thread, summed, chunk bits
+    for (int rev = 0; rev < 2; rev++)
+      for (const Op& op : rev ? p.bwd : p.fwd)
+        if (op.kind == OpKind::Row && op.row.k_split_bits >= 0)
+          printf("%d %d %d %d %d\n", rev, op.row.n_rows, op.row.n_in, op.row.n_k, op.row.k_split_bits);
+    return 0;
   }
   g_slot.resize((size_t)p.n_slots);
   FILE* in = fopen(argv[2], "rb");

@@ -36,12 +36,16 @@ def emu(tmp_path_factory):
     return out
 
 
-def run(emu, d, net, tree, prec, wrt, go, sliced=(), ids=(0,), grouped=True):
+def describe(d, net, tree, sliced, ids, wrt, opt):
     lists = [[len(t) for t in net.leaf_idx], [i for t in net.leaf_idx for i in t], list(net.idx_dim), list(net.out_idx),
-             list(tree.left), list(tree.right), list(sliced), list(ids), list(wrt), [PREC[prec], 0, int(grouped)]]
+             list(tree.left), list(tree.right), list(sliced), list(ids), list(wrt), opt]
     with open(os.path.join(d, "net.txt"), "w") as f:
         for x in lists:
             f.write(" ".join(str(int(v)) for v in [len(x)] + x) + "\n")
+
+
+def run(emu, d, net, tree, prec, wrt, go, sliced=(), ids=(0,), grouped=True):
+    describe(d, net, tree, sliced, ids, wrt, [PREC[prec], 0, int(grouped)])
     with open(os.path.join(d, "in.bin"), "wb") as f:
         for t in list(net.leaves) + [go]:
             np.ascontiguousarray(t, dtype=np.complex128).tofile(f)
@@ -111,6 +115,40 @@ def test_random_program_sliced(emu, oracle_lib, tmp_path):
     net, tree = random_case(*GRAPHS[0])
     sliced = [e for e in range(net.n_idx) if e not in net.out_idx][:3]
     check(emu, oracle_lib, tmp_path, net, tree, list(range(net.n_leaves)), sliced=sliced, ids=(0, 3, 5))
+
+
+def _chain(k, ks):
+    """Additions a value passes: its lane's, then the chunks' (64 lanes and a butterfly)."""
+    return 2 ** (k - 6 - ks) + (2 ** (ks - 6) + 6 if ks > 6 else ks)
+
+
+@pytest.mark.parametrize("prec", PREC)
+@pytest.mark.parametrize("m,n", [(0, 0), (1, 0), (1, 1), (2, 1), (3, 2), (5, 2), (8, 4), (10, 0), (10, 4), (13, 0)])
+def test_length_of_split_sums(emu, tmp_path, m, n, prec):
+    """A split sum in any program passes at most the additions that 2^15
+    wavefronts (rows x chunks) give it, whatever order the operands hold the
+    summed bits in."""
+    seen = 0
+    for k in range(6, 30):
+        if m + k > 30:
+            break
+        M, N, K = list(range(m)), list(range(m, m + n)), list(range(m + n, m + n + k))
+        z = m + n + k
+        for order in (K, K[::-1]):
+            # node 1 = A B, then a vector: the reverse program sums node 1 again
+            net = Network([np.zeros(())] * 3, [M + K, N + order, [z]], [2] * (z + 1), M + N + [z])
+            tree = Tree(np.array([0, 3], np.int32), np.array([1, 2], np.int32))
+            describe(str(tmp_path), net, tree, (), (0,), [2], [PREC[prec], 0, 0, 1])
+            out = subprocess.run([emu, str(tmp_path / "net.txt"), "-", "-"], capture_output=True, text=True, check=True).stdout
+            for line in out.splitlines():
+                rev, rows, inner, kk, ks = map(int, line.split())
+                if kk != k:
+                    continue
+                most = min(k - 6, max(0, 15 - (m + n - min(4, min(m, n)))))
+                most2 = min(k - 6, max(0, 15 - (m + n - min(4, max(m, n)))))
+                assert _chain(k, ks) <= max(_chain(k, most), _chain(k, most2)), (rev, m, n, k, ks)
+                seen += 1
+    assert seen > 20
 
 
 @pytest.mark.gpu
