@@ -382,16 +382,20 @@ static Op split_op(const Ref& src, const int8_t* fpos, int nf, const int8_t* hpo
 // h, fa, fb and k summed bits (sum split in 2^ks chunks, one wavefront per row
 // and chunk, when `splitk`).  All that fit from 2^16 rows (2^13 wavefronts) on;
 // below, as few as bring the rows to 2^16 threads (one per SIMD lane of the
-// chip), or the wavefronts to 2^12.  A small tensor applied to every row keeps
-// them all: its streaming kernel needs B to have no row bit.  Measured: launches
-// of 2^10 rows x 16 outputs 12-16 us, the same as 2^14 rows x 1 output 5.6-8.3
-// us (a random graph of 120 tensors in complex128 588 -> 516 us per call).
-static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool splitk, int ks) {
+// chip), or the wavefronts to 2^12.  `slices` of them are in flight in one
+// launch.  A small tensor applied to every row keeps them all: its streaming
+// kernel needs B to have no row bit.  Measured: launches of 2^10 rows x 16
+// outputs 12-16 us, the same as 2^14 rows x 1 output 5.6-8.3 us (a random graph
+// of 120 tensors in complex128 588 -> 516 us per call); 64 slices of 2^12 rows x
+// 16 outputs x 2^5 summed values 118 us per call, as 2^16 rows x 1 output 301.
+static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool splitk, int ks, int slices) {
   const int most = std::min(fb, kMaxInThread), outs = h + fa + fb, rows = outs - most;
-  if (splitk) return rows + ks >= 13 ? most : std::max(0, std::min(most, outs + ks - 12));
-  if (rows >= 16) return most;
+  int log_slices = 0;
+  while ((slices >> log_slices) > 1) log_slices++;
+  if (splitk) return rows + ks + log_slices >= 13 ? most : std::max(0, std::min(most, outs + ks + log_slices - 12));
+  if (rows + log_slices >= 16) return most;
   if (!accumulate && h == 0 && fb == most && rows >= 6 && k <= 2 && most + k <= 4) return most;
-  return std::max(0, std::min(most, outs - 16));
+  return std::max(0, std::min(most, outs + log_slices - 16));
 }
 
 // Most additions that a value of a split-K op passes, one after another: a
@@ -559,7 +563,7 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     // spread over the chip: a thread (a wavefront of split sums) with 16 of
     // them is a long serial chain next to idle compute units.  Every output
     // keeps its order of summation.
-    const int nin = narrow ? fb : in_thread_bits(h, fa, fb, k, accumulate, splitk, ks);
+    const int nin = narrow ? fb : in_thread_bits(h, fa, fb, k, accumulate, splitk, ks, p->n_batch);
     std::vector<int> rows = H;
     rows.insert(rows.end(), FA.begin(), FA.end());
     rows.insert(rows.end(), FB.begin() + nin, FB.end());
@@ -879,29 +883,37 @@ int build_plan(tn_plan_s* p, std::string& err) {
   const int n = p->n_leaves, nn = 2 * n - 1;
   // forward program: one contraction per internal node in tree order; the
   // root's value stays in the arena for the mode-specific tail
-  Prog prog;
-  prog.ops.reserve((size_t)n + n / 4);
-  std::vector<int> bufs(nn, -1);
-  for (int v = n; v < nn; v++) bufs[v] = prog.new_buf(node_bytes(p, v));
-  for (int k = 0; k < n - 1; k++) {
-    int v = n + k;
-    NodeInfo& ni = p->nodes[k];
-    Operand A = node_operand(p, ni.l, bufs), B = node_operand(p, ni.r, bufs);
-    Op op = make_contract(p, A, B, 0, 0, buf_ref(bufs[v]), p->layout[v], false, ni.swap ? 1 : 0, v, prog);
-    ni.flops = op.flops;
-    ni.bytes = op.bytes;
-    ni.kclass = op.kind == OpKind::Gemm ? (op.gemm.k_split_bits > 0 ? kGemmSplitK : kGemm)
-                                        : (op.row.k_split_bits >= 0 ? kSplitK : kRow);
-    ni.k_split_bits = op.row.k_split_bits;
-    push(prog, op);
-  }
-  p->arena_bytes = std::max<uint64_t>(allocate_grouped(p, prog, n > 1 ? bufs[nn - 1] : -1,
-                                                      [&](uint64_t x, uint64_t y) { return arena_ok(p, x, y); }), 256);
-  p->fwd = std::move(prog.ops);
-  p->root_off = n > 1 ? prog.bufs[(size_t)bufs[nn - 1]].off : -1;
-  // in-flight slices
+  auto forward = [&] {
+    Prog prog;
+    prog.ops.reserve((size_t)n + n / 4);
+    std::vector<int> bufs(nn, -1);
+    for (int v = n; v < nn; v++) bufs[v] = prog.new_buf(node_bytes(p, v));
+    for (int k = 0; k < n - 1; k++) {
+      int v = n + k;
+      NodeInfo& ni = p->nodes[k];
+      Operand A = node_operand(p, ni.l, bufs), B = node_operand(p, ni.r, bufs);
+      Op op = make_contract(p, A, B, 0, 0, buf_ref(bufs[v]), p->layout[v], false, ni.swap ? 1 : 0, v, prog);
+      ni.flops = op.flops;
+      ni.bytes = op.bytes;
+      ni.kclass = op.kind == OpKind::Gemm ? (op.gemm.k_split_bits > 0 ? kGemmSplitK : kGemm)
+                                          : (op.row.k_split_bits >= 0 ? kSplitK : kRow);
+      ni.k_split_bits = op.row.k_split_bits;
+      push(prog, op);
+    }
+    p->arena_bytes = std::max<uint64_t>(allocate_grouped(p, prog, n > 1 ? bufs[nn - 1] : -1,
+                                                        [&](uint64_t x, uint64_t y) { return arena_ok(p, x, y); }), 256);
+    p->fwd = std::move(prog.ops);
+    p->root_off = n > 1 ? prog.bufs[(size_t)bufs[nn - 1]].off : -1;
+  };
+  // in-flight slices: asked for, or as many as the arena lets the cap hold
+  // (the arena does not depend on their number)
+  p->n_batch = p->opt.max_inflight_slices > 0 ? inflight(p, 0) : 1;
+  forward();
   const int nb = inflight(p, p->arena_bytes);
-  p->n_batch = nb;
+  if (nb != p->n_batch) {
+    p->n_batch = nb;
+    forward();
+  }
   int64_t max_ids = std::min<int64_t>(std::max<int64_t>(p->d_sliced, nb), int64_t(1) << 22);
   max_ids = (max_ids + nb - 1) / nb * nb;
   // slots: leaves, out, grad_out, then gradients (sized for every leaf)

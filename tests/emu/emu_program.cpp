@@ -284,7 +284,7 @@ int main(int argc, char** argv) {
   p.sliced = list<int64_t>(f);
   const std::vector<int64_t> ids = list<int64_t>(f);
   const std::vector<int32_t> wrt = list<int32_t>(f);
-  const std::vector<int32_t> opt = list<int32_t>(f);       // precision, flags, group_small[, list split contractions only]
+  const std::vector<int32_t> opt = list<int32_t>(f);       // precision, flags, group_small[, slices in flight: list the row ops only]
   fclose(f);
   const int nl = p.n_leaves = (int)p.rank.size();
   p.n_idx = (int)p.idx_dim.size();
@@ -294,16 +294,17 @@ int main(int argc, char** argv) {
   p.opt.prec = opt[0];
   p.opt.flags = opt[1];
   p.group_small = opt[2] != 0;
+  if (opt.size() > 3) p.opt.max_inflight_slices = opt[3];
   g_eb = p.elem_bytes = p.prec == TN_C128 ? 16 : 8;
   std::string err;
   if (build_plan(&p, err) || (!wrt.empty() && build_backward(&p, wrt, err))) {
     fprintf(stderr, "plan: %s\n", err.c_str());
     return 2;
   }
-  if (opt.size() > 3) {                                    // split contractions: reverse, rows, in-thread, summed, chunk bits
+  if (opt.size() > 3) {                                    // row ops: reverse, rows, in-thread, summed, chunk bits
     for (int rev = 0; rev < 2; rev++)
       for (const Op& op : rev ? p.bwd : p.fwd)
-        if (op.kind == OpKind::Row && op.row.k_split_bits >= 0)
+        if (op.kind == OpKind::Row)
           printf("%d %d %d %d %d\n", rev, op.row.n_rows, op.row.n_in, op.row.n_k, op.row.k_split_bits);
     return 0;
   }

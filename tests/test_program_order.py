@@ -117,6 +117,13 @@ def test_random_program_sliced(emu, oracle_lib, tmp_path):
     check(emu, oracle_lib, tmp_path, net, tree, list(range(net.n_leaves)), sliced=sliced, ids=(0, 3, 5))
 
 
+def row_ops(emu, tmp_path, net, tree, sliced, wrt, prec, inflight):
+    """(reverse, log2 rows, in-thread outputs, summed values, chunks or -1) of every row and split-K contraction."""
+    describe(str(tmp_path), net, tree, sliced, (0,), wrt, [PREC[prec], 0, 0, inflight])
+    out = subprocess.run([emu, str(tmp_path / "net.txt"), "-", "-"], capture_output=True, text=True, check=True).stdout
+    return [tuple(map(int, line.split())) for line in out.splitlines()]
+
+
 def _chain(k, ks):
     """Additions a value passes: its lane's, then the chunks' (64 lanes and a butterfly)."""
     return 2 ** (k - 6 - ks) + (2 ** (ks - 6) + 6 if ks > 6 else ks)
@@ -138,17 +145,27 @@ def test_length_of_split_sums(emu, tmp_path, m, n, prec):
             # node 1 = A B, then a vector: the reverse program sums node 1 again
             net = Network([np.zeros(())] * 3, [M + K, N + order, [z]], [2] * (z + 1), M + N + [z])
             tree = Tree(np.array([0, 3], np.int32), np.array([1, 2], np.int32))
-            describe(str(tmp_path), net, tree, (), (0,), [2], [PREC[prec], 0, 0, 1])
-            out = subprocess.run([emu, str(tmp_path / "net.txt"), "-", "-"], capture_output=True, text=True, check=True).stdout
-            for line in out.splitlines():
-                rev, rows, inner, kk, ks = map(int, line.split())
-                if kk != k:
+            for rev, _, _, kk, ks in row_ops(emu, tmp_path, net, tree, (), [2], prec, 1):
+                if kk != k or ks < 0:
                     continue
                 most = min(k - 6, max(0, 15 - (m + n - min(4, min(m, n)))))
                 most2 = min(k - 6, max(0, 15 - (m + n - min(4, max(m, n)))))
                 assert _chain(k, ks) <= max(_chain(k, most), _chain(k, most2)), (rev, m, n, k, ks)
                 seen += 1
     assert seen > 20
+
+
+@pytest.mark.parametrize("prec", PREC)
+@pytest.mark.parametrize("m,k,slices,inner", [(12, 5, 0, 0), (12, 5, 1, 1), (12, 5, 4, 4), (12, 5, 6, 4), (8, 5, 0, 0), (8, 5, 6, 2),
+                                              (8, 10, 0, 4), (5, 9, 0, 0), (5, 9, 2, 2), (5, 9, 6, 4), (16, 5, 0, 4)])
+def test_outputs_per_thread(emu, tmp_path, m, k, slices, inner, prec):
+    """2^m rows x 16 outputs: as few of the 16 stay in one thread as fill the
+    chip with the slices in flight (2^16 threads, or 2^12 wavefronts of split
+    sums), all of them where the rows do."""
+    M, N, K, S = [list(range(*r)) for r in ((0, m), (m, m + 4), (m + 4, m + 4 + k), (m + 4 + k, m + 4 + k + slices))]
+    net = Network([np.zeros(())] * 2, [S + M + K, S + N + K], [2] * (m + 4 + k + slices), M + N)
+    ops = row_ops(emu, tmp_path, net, Tree(np.array([0], np.int32), np.array([1], np.int32)), S, [], prec, 2 ** slices)
+    assert [(op[1], op[2]) for op in ops] == [(m + 4 - inner, inner)]
 
 
 @pytest.mark.gpu
