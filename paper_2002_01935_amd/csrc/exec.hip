@@ -257,7 +257,7 @@ static const char* op_kernel_name(const tn_plan_s* p, const Op& op, int* tile) {
     case OpKind::Gemm:
       if (gemm_smallk_ok(op.gemm)) return smallk_kernel_name(op.gemm, p->prec);
       *tile = p->prec == TN_C128 ? kValuTile : op.gemm.tile;
-      return gemm_kernel_name(op.gemm, p->prec);
+      return gemm_kernel_name(op.gemm, p->prec, p->n_batch);
     case OpKind::Accum: return "accum_kernel";
     case OpKind::Permute: return "permute_kernel";
     case OpKind::Counter: return "counter_kernel";

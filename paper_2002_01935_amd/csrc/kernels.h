@@ -42,13 +42,14 @@ unsigned stream_grid_x(uint64_t waves, unsigned gy, const void* kernel);
 int gemm_tile_bits(int tile, int* bm, int* bn);
 // whether tile variant `tile` can run op at precision prec
 bool gemm_tile_ok(const GemmOp& op, int tile, int prec);
-// kernel (template instance) that launch_gemm runs for op's tile at precision prec
-const char* gemm_kernel_name(const GemmOp& op, int prec);
+// kernel (template instance) that launch_gemm runs for op's tile at precision
+// prec with `slices` in flight
+const char* gemm_kernel_name(const GemmOp& op, int prec, int slices);
 constexpr int kNumGemmTiles = 17;
 constexpr int kSplitTile = 10;      // first BF16x3 variant on pre-split operands (direct-to-LDS)
 constexpr int kNumSplitTiles = 4;   // variants 10, 11, 12, 13
 constexpr int kNumTilesShared = 4;   // tiles 0..3 exist for every matrix-core kernel
 constexpr int kSmallTileDl = 15, kSmallTile = 16;   // 64 x 64, four waves of 32 x 32 (4M)
-constexpr int kValuTile = 4;   // vector-ALU variant (complex128 and reference)
+constexpr int kValuTile = 4;   // vector-ALU variant (FP32 reference); complex128: gemm_mfma_f64
 
 }  // namespace tn

@@ -1904,15 +1904,17 @@ bool gemm_tile_ok(const GemmOp& op, int tile, int prec) {
 // operand value it reads from LDS for more products, but needs two blocks per
 // compute unit to hide its barriers; with fewer, 64 x 64 tiles fill the chip,
 // and below two of those per unit 32 x 64 (2^10 x 2^10 x 2^8 87 -> 80 us, 2^8 x 2^10 x 2^7 56 -> 40 per call).
-static int f64_tile_bits(const GemmOp& op) {
-  const int rest = std::max(0, op.n_n - 6) + op.n_h + std::max(0, op.k_split_bits);
+// The blocks of all slices of a launch count; the tile does not change the sums.
+static int f64_tile_bits(const GemmOp& op, int slices) {
+  int rest = std::max(0, op.n_n - 6) + op.n_h + std::max(0, op.k_split_bits);
+  while (slices > 1) { rest++; slices >>= 1; }
   if (op.n_m >= 7 && op.n_m - 7 + rest >= 9) return 7;
   return std::max(0, op.n_m - 6) + rest >= 9 ? 6 : 5;
 }
 
-const char* gemm_kernel_name(const GemmOp& op, int prec) {
+const char* gemm_kernel_name(const GemmOp& op, int prec, int slices) {
   if (prec == TN_C128) {
-    const int bits = f64_tile_bits(op);
+    const int bits = f64_tile_bits(op, slices);
     return bits == 7 ? "gemm_mfma_f64<128,64,8,2,2>" : (bits == 6 ? "gemm_mfma_f64<64,64,8,2,2>" : "gemm_mfma_f64<32,64,8,2,2>");
   }
   if (op.tile == kValuTile) return "gemm_valu<float>";
@@ -1993,7 +1995,7 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
   if (prec == TN_C128) tile = 4;
   op.tile = tile;
   if (gemm_tile_bits(tile, &bm, &bn) || !gemm_tile_ok(op, tile, prec)) return hipErrorInvalidValue;
-  if (prec == TN_C128) bm = f64_tile_bits(op);
+  if (prec == TN_C128) bm = f64_tile_bits(op, ctx.n_batch);
   const int tm = op.n_m < bm ? op.n_m : bm, tn = op.n_n < bn ? op.n_n : bn;
   const uint64_t tiles = uint64_t(1) << ((op.n_m - tm) + (op.n_n - tn));
   const uint64_t gy = uint64_t(ctx.n_batch) << op.n_h;
@@ -2020,7 +2022,7 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
 static hipError_t launch_gemm_kernel(const Ctx& ctx, const GemmOp& op, int prec, dim3 grid, hipStream_t s) {
   const int tile = op.tile;
   if (prec == TN_C128) {
-    switch (f64_tile_bits(op)) {
+    switch (f64_tile_bits(op, ctx.n_batch)) {
       case 7: hipLaunchKernelGGL((gemm_mfma_f64<128, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;
       case 6: hipLaunchKernelGGL((gemm_mfma_f64<64, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;
       default: hipLaunchKernelGGL((gemm_mfma_f64<32, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op);
