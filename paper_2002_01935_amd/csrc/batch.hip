@@ -268,7 +268,7 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
     t.conj_a = r.conj_a; t.conj_b = r.conj_b;
   } else if (op.kind == OpKind::Gemm) {
     const GemmOp& g = op.gemm;
-    if (g.accumulate || g.ab_split || g.k_split_bits > 0 || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
+    if (g.accumulate || g.ab_split || g.k_split_bits + g.k_fold_bits > 0 || !fits(g.n_h + g.n_m + g.n_n, g.n_k)) return false;
     if (t.n_out + t.n_k > kLevelGemmBits) return false;
     int j = 0;
     for (int i = 0; i < g.n_h; i++, j++) { oa[j] = g.a_h[i]; ob[j] = g.b_h[i]; oc[j] = g.c_h[i]; }

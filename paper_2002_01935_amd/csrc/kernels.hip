@@ -1409,8 +1409,9 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
 
 // ------------------------------------------------------------------ split-K sum
 
-// Fixed-order sum of the split-K partial products of a GEMM (splits in
-// increasing order, so the result does not depend on scheduling): element e
+// Fixed-order sum of the split-K partial products of a GEMM (blocks of
+// 2^n_inner splits in increasing order, the splits of a block likewise, so the
+// result does not depend on scheduling): element e
 // = (h, m, n) of every split, n fastest, goes to C at the positions of its h,
 // m and n bits.
 struct SplitReduceOp {
@@ -1418,7 +1419,9 @@ struct SplitReduceOp {
   BitRuns run_c;       // C positions of the bits of e
   int32_t n_e;         // log2 elements per split
   int32_t n_split;     // log2 splits
+  int32_t n_inner;     // log2 splits of a block
   int32_t accumulate;  // add into C instead of overwriting
+  int32_t pad;
 };
 
 template <typename T>
@@ -1430,13 +1433,22 @@ __global__ __launch_bounds__(256) void split_reduce_kernel(Ctx ctx, SplitReduceO
   const uint64_t e = uint64_t(blockIdx.x) * 256 + threadIdx.x;
   if (e >> op.n_e) return;
   GMEM const V* P = reinterpret_cast<GMEM const V*>(resolve(ctx, op.part, z, sid, sizeof(V))) + e;
-  V acc = ld(P);
-  const uint64_t ns = uint64_t(1) << op.n_split;
+  const uint64_t ni = uint64_t(1) << (op.n_inner > 0 ? op.n_inner : op.n_split), ns = uint64_t(1) << op.n_split;
+  V acc;
+  for (uint64_t s0 = 0; s0 < ns; s0 += ni) {
+    V in = ld(P + (s0 << op.n_e));
 #pragma unroll 8
-  for (uint64_t sp = 1; sp < ns; sp++) {
-    const V v = ld(P + (sp << op.n_e));
-    acc.x += v.x;
-    acc.y += v.y;
+    for (uint64_t sp = 1; sp < ni; sp++) {
+      const V v = ld(P + ((s0 + sp) << op.n_e));
+      in.x += v.x;
+      in.y += v.y;
+    }
+    if (s0 == 0) {
+      acc = in;
+    } else {
+      acc.x += in.x;
+      acc.y += in.y;
+    }
   }
   GMEM V* C = reinterpret_cast<GMEM V*>(resolve(ctx, op.c, z, sid, sizeof(V))) + deposit_runs(e, op.run_c);
   if (op.accumulate) {
@@ -1466,7 +1478,8 @@ typedef double doublex4 __attribute__((ext_vector_type(4)));
 // 81 % busy).  Against the vector-ALU kernel before: 2^12 x 2^12 x 2^12 13.2 ->
 // 8.64 ms, 2^10 x 2^13 x 2^10 1.72 -> 1.17 ms, 2^7 x 2^9 x 2^11 (split) 248 ->
 // 71 us per call.
-template <int BM, int BN, int BK, int WGM, int WGN>
+// FOLD: the sum is cut into 2^k_fold_bits parts that are added in order.
+template <int BM, int BN, int BK, int WGM, int WGN, bool FOLD = false>
 __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(2))) void gemm_mfma_f64(Ctx ctx, GemmOp op) {
   constexpr int RK = __builtin_ctz(BK), LDR = 2 * BK + 2;
   constexpr int NT = 64 * WGM * WGN;
@@ -1546,6 +1559,8 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
   for (int i = 0; i < FM; i++)
 #pragma unroll
     for (int j = 0; j < FN; j++) acc[i][j] = doublex4{0, 0, 0, 0};
+  doublex4 total[FOLD ? FM : 1][FOLD ? FN : 1];
+  const uint64_t part_steps = FOLD ? nsteps >> op.k_fold_bits : nsteps;
 
   gload();
   sstore(0);
@@ -1566,7 +1581,25 @@ __global__ __launch_bounds__(64 * WGM * WGN) __attribute__((amdgpu_waves_per_eu(
         for (int i = 0; i < FM; i++) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[i], fb[j], acc[i][j], 0, 0, 0);
     }
     if (s + 1 < nsteps) sstore(buf ^ 1);
+    if constexpr (FOLD) {
+      if (((s + 1) & (part_steps - 1)) == 0) {
+        const bool first = s < part_steps;
+#pragma unroll
+        for (int i = 0; i < FM; i++)
+#pragma unroll
+          for (int j = 0; j < FN; j++) {
+            total[i][j] = first ? acc[i][j] : total[i][j] + acc[i][j];
+            acc[i][j] = doublex4{0, 0, 0, 0};
+          }
+      }
+    }
     __syncthreads();
+  }
+  if constexpr (FOLD) {
+#pragma unroll
+    for (int i = 0; i < FM; i++)
+#pragma unroll
+      for (int j = 0; j < FN; j++) acc[i][j] = total[i][j];
   }
   // accumulator r of lane l: row 4 r + l / 16, real column l % 16
   GMEM double* C = reinterpret_cast<GMEM double*>(resolve(ctx, op.c, g.z, g.sid, 16));
@@ -1908,13 +1941,15 @@ bool gemm_tile_ok(const GemmOp& op, int tile, int prec) {
 static int f64_tile_bits(const GemmOp& op, int slices) {
   int rest = std::max(0, op.n_n - 6) + op.n_h + std::max(0, op.k_split_bits);
   while (slices > 1) { rest++; slices >>= 1; }
-  if (op.n_m >= 7 && op.n_m - 7 + rest >= 9) return 7;
+  // (a folded sum needs the accumulators twice, too many registers for 128 x 64)
+  if (op.n_m >= 7 && op.n_m - 7 + rest >= 9 && op.k_fold_bits == 0) return 7;
   return std::max(0, op.n_m - 6) + rest >= 9 ? 6 : 5;
 }
 
 const char* gemm_kernel_name(const GemmOp& op, int prec, int slices) {
   if (prec == TN_C128) {
     const int bits = f64_tile_bits(op, slices);
+    if (op.k_fold_bits > 0) return bits == 6 ? "gemm_mfma_f64<64,64,8,2,2,fold>" : "gemm_mfma_f64<32,64,8,2,2,fold>";
     return bits == 7 ? "gemm_mfma_f64<128,64,8,2,2>" : (bits == 6 ? "gemm_mfma_f64<64,64,8,2,2>" : "gemm_mfma_f64<32,64,8,2,2>");
   }
   if (op.tile == kValuTile) return "gemm_valu<float>";
@@ -2007,6 +2042,8 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
   r.c = in.c;
   r.n_e = e_bits;
   r.n_split = ks;
+  r.n_inner = in.k_inner_bits;
+  r.pad = 0;
   r.accumulate = in.accumulate;
   int8_t pos[kMaxBits];
   for (int j = 0; j < in.n_n; j++) pos[j] = in.c_n[j];
@@ -2022,6 +2059,12 @@ hipError_t launch_gemm(const Ctx& ctx, const GemmOp& in, int prec, hipStream_t s
 static hipError_t launch_gemm_kernel(const Ctx& ctx, const GemmOp& op, int prec, dim3 grid, hipStream_t s) {
   const int tile = op.tile;
   if (prec == TN_C128) {
+    if (op.k_fold_bits > 0) {
+      if (op.n_k - op.k_fold_bits < 3) return hipErrorInvalidValue;   // whole steps of eight summed values
+      if (f64_tile_bits(op, ctx.n_batch) == 6) hipLaunchKernelGGL((gemm_mfma_f64<64, 64, 8, 2, 2, true>), grid, dim3(256), 0, s, ctx, op);
+      else hipLaunchKernelGGL((gemm_mfma_f64<32, 64, 8, 2, 2, true>), grid, dim3(256), 0, s, ctx, op);
+      return hipGetLastError();
+    }
     switch (f64_tile_bits(op, ctx.n_batch)) {
       case 7: hipLaunchKernelGGL((gemm_mfma_f64<128, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;
       case 6: hipLaunchKernelGGL((gemm_mfma_f64<64, 64, 8, 2, 2>), grid, dim3(256), 0, s, ctx, op); break;

@@ -378,6 +378,18 @@ static Op split_op(const Ref& src, const int8_t* fpos, int nf, const int8_t* hpo
   return o;
 }
 
+static int log2_floor(int x) {
+  int l = 0;
+  while ((x >> l) > 1) l++;
+  return l;
+}
+
+// log2 of the 64 x 64 blocks (slices in flight included) from which a
+// complex128 GEMM is not split over the grid for parallelism: one per compute
+// unit.  16 slices of 2^7 x 2^9 x 2^11: 379 us per call, split 436; 4 of 2^5 x
+// 2^5 x 2^15 98 and 284; below, 2 of 2^8 x 2^8 x 2^11 96 and 85.
+constexpr int kFoldBlocks = 8;
+
 // In-thread free bits of a row op with batch, row-side and in-thread-side bits
 // h, fa, fb and k summed bits (sum split in 2^ks chunks, one wavefront per row
 // and chunk, when `splitk`).  All that fit from 2^16 rows (2^13 wavefronts) on;
@@ -389,9 +401,7 @@ static Op split_op(const Ref& src, const int8_t* fpos, int nf, const int8_t* hpo
 // of 120 tensors in complex128 588 -> 516 us per call); 64 slices of 2^12 rows x
 // 16 outputs x 2^5 summed values 118 us per call, as 2^16 rows x 1 output 301.
 static int in_thread_bits(int h, int fa, int fb, int k, bool accumulate, bool splitk, int ks, int slices) {
-  const int most = std::min(fb, kMaxInThread), outs = h + fa + fb, rows = outs - most;
-  int log_slices = 0;
-  while ((slices >> log_slices) > 1) log_slices++;
+  const int most = std::min(fb, kMaxInThread), outs = h + fa + fb, rows = outs - most, log_slices = log2_floor(slices);
   if (splitk) return rows + ks + log_slices >= 13 ? most : std::max(0, std::min(most, outs + ks + log_slices - 12));
   if (rows + log_slices >= 16) return most;
   if (!accumulate && h == 0 && fb == most && rows >= 6 && k <= 2 && most + k <= 4) return most;
@@ -510,13 +520,23 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     // complex64 results are gradients; complex64 forward values keep the sums
     // they had): 64 x 64 tiles fill the chip with 2^9 blocks, each summing at
     // least 2^6 values (about 7 us of FP64 matrix-core work, 3.5 us in FP32);
-    // the partial buffer stays at most as large as the larger operand
-    if (p->prec == TN_C128 ? p->split_f64 : p->reverse) {
+    // the partial buffer stays at most as large as the larger operand.  In
+    // complex128 the sum has that order also where the workspace has no room
+    // for the partial tiles (split_f64 off), so that a value does not depend
+    // on the number of slices in flight.
+    ks = std::max(ks, 0);
+    if (p->prec == TN_C128 || p->reverse) {
       const int tiles64 = std::max(0, fa - 6) + std::max(0, fb - 6) + h;
-      ks = std::max(ks, std::min(std::min(k - 6, 9 - tiles64), std::max(h + fa + k, h + fb + k) - (h + fa + fb)));
-      ks = std::min(ks, 10);
+      const int more = std::min(std::min(k - 6, 9 - tiles64), std::max(h + fa + k, h + fb + k) - (h + fa + fb));
+      const int inner = std::max(0, std::min(more, 10) - ks);
+      if (p->prec == TN_C128 && (!p->split_f64 || tiles64 + ks + log2_floor(p->n_batch) >= kFoldBlocks)) {
+        g.k_fold_bits = inner;
+      } else {
+        ks += inner;
+        g.k_inner_bits = p->prec == TN_C128 ? inner : 0;
+      }
     }
-    g.k_split_bits = ks > 0 ? ks : 0;
+    g.k_split_bits = ks;
     if (ks > 0) g.part = buf_ref(prog.new_buf((int64_t)p->elem_bytes << (h + fa + fb + ks)));
     // BF16x3: split both operands once into the planes the matrix-core kernel
     // streams (the GEMM then reads them instead of A and B)
@@ -905,15 +925,25 @@ int build_plan(tn_plan_s* p, std::string& err) {
     p->fwd = std::move(prog.ops);
     p->root_off = n > 1 ? prog.bufs[(size_t)bufs[nn - 1]].off : -1;
   };
-  // in-flight slices: asked for, or as many as the arena lets the cap hold
-  // (the arena does not depend on their number)
-  p->n_batch = p->opt.max_inflight_slices > 0 ? inflight(p, 0) : 1;
+  // in-flight slices: asked for, or as many as the cap holds of the arena
+  // without the partial tiles of splits for parallelism (which are then taken
+  // only if as many slices still fit)
+  const uint64_t cap = p->opt.max_inflight_slices > 0 ? 0 : p->opt.workspace_cap;
+  const bool split = p->split_f64;
+  p->n_batch = cap ? 1 : inflight(p, 0);
+  if (cap) p->split_f64 = false;
   forward();
-  const int nb = inflight(p, p->arena_bytes);
-  if (nb != p->n_batch) {
-    p->n_batch = nb;
-    forward();
+  if (cap) {
+    const uint64_t bytes = p->arena_bytes;
+    p->n_batch = inflight(p, bytes);
+    p->split_f64 = split;
+    if (p->n_batch > 1 || (split && p->prec == TN_C128)) forward();
+    if (p->arena_bytes > bytes && (inflight(p, p->arena_bytes) < p->n_batch || p->arena_bytes > cap)) {
+      p->split_f64 = false;
+      forward();
+    }
   }
+  const int nb = p->n_batch;
   int64_t max_ids = std::min<int64_t>(std::max<int64_t>(p->d_sliced, nb), int64_t(1) << 22);
   max_ids = (max_ids + nb - 1) / nb * nb;
   // slots: leaves, out, grad_out, then gradients (sized for every leaf)

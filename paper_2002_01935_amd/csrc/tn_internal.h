@@ -108,8 +108,13 @@ struct GemmOp {
   // produces C.  Set at launch for the kernels: the positions of the split
   // bits in A and B as runs, and the element stride between splits of the
   // partial buffer (0 when the grid's z dimension is 1).
+  // complex128: the sum over the k_inner_bits lowest split bits is taken first
+  // (the partial tiles of a block of 2^k_inner_bits splits, then the blocks);
+  // k_fold_bits of them are summed inside the kernel instead of over the grid,
+  // in the same order, so that both give the same bits.
   Ref part;
   int32_t k_split_bits;
+  int32_t k_inner_bits, k_fold_bits;
   int32_t c_split_shift;
   BitRuns run_a_s, run_b_s;
   // BF16x3 on pre-split operands: a and b point to SplitOp outputs (planes in
