@@ -2,9 +2,10 @@
 
 Every step of a contraction runs in libtn's HIP kernels.  PyTorch supplies
 device memory (leaves, outputs, gradients, workspace) and the stream
-(torch.cuda.current_stream()).  If libtn.so or _leaves.so (leaf checks, host
-code) is missing this module raises on import: there is no fallback
-implementation.
+(torch.cuda.current_stream()).  If libtn.so is missing this module raises on
+import: there is no fallback implementation.  The checks of lists of leaf
+tensors are host code in _leaves.so; for objects that only look like tensors,
+and with a warning where that extension cannot be loaded, they run in Python.
 """
 
 from __future__ import annotations
@@ -12,6 +13,7 @@ from __future__ import annotations
 import ctypes
 import math
 import os
+import warnings
 
 import numpy as np
 # torch first: it carries its own HIP / HSA runtime libraries, and libtn.so must
@@ -85,7 +87,12 @@ def _load():
 
 
 lib = _load()
-from . import _leaves  # noqa: E402
+try:
+    from . import _leaves
+except ImportError as e:
+    _leaves = None
+    warnings.warn(f"leaf checks run in Python, a microsecond per leaf ({e}); "
+                  "run `python -m paper_2002_01935_amd.build`")
 
 
 def _check(rc):
@@ -120,7 +127,13 @@ def _on_stream(stream, make):
 
 
 def _dev_ptrs(tensors):
-    return _leaves.pointers(tensors)
+    """The addresses of `tensors` (or of objects with a data_ptr method), 8 bytes each."""
+    if _leaves is not None:
+        try:
+            return _leaves.pointers(tensors)
+        except TypeError:
+            pass
+    return bytes((ctypes.c_uint64 * len(tensors))(*[t.data_ptr() for t in tensors]))
 
 
 class Plan:
@@ -138,7 +151,8 @@ class Plan:
         for r in rank:
             self.leaf_shapes.append(tuple(int(idx_dim[e]) for e in leaf_idx[off:off + r]))
             off += r
-        self._leaf_sizes = np.array([math.prod(s) for s in self.leaf_shapes], np.int64).tobytes()
+        # (a leaf too large for int64 is tn_plan's to refuse)
+        self._leaf_sizes = np.array([max(-1, min(math.prod(s), 2 ** 63 - 1)) for s in self.leaf_shapes], np.int64).tobytes()
         self.precision = precision
         self.prec = PRECISIONS[precision]
         keep = []
@@ -232,13 +246,19 @@ class Plan:
         """The leaves' device addresses (the pointer array the library takes)."""
         if len(leaves) != self.n_leaves:
             raise ValueError(f"expected {self.n_leaves} leaves, got {len(leaves)}")
-        ptrs = _leaves.leaves(leaves, self.prec == TN_C128, self._leaf_sizes)
-        if isinstance(ptrs, int):
-            v, t = ptrs, leaves[ptrs]
+        if _leaves is not None:
+            try:
+                ptrs = _leaves.leaves(leaves, self.prec == TN_C128, self._leaf_sizes)
+                if isinstance(ptrs, bytes):
+                    return ptrs
+            except TypeError:   # not all of them are tensors
+                pass
+        for v, t in enumerate(leaves):
             if not t.is_cuda or not t.is_contiguous() or t.dtype != self.storage_dtype:
                 raise ValueError(f"leaf {v} must be a contiguous {self.storage_dtype} CUDA tensor")
-            raise ValueError(f"leaf {v} has shape {tuple(t.shape)}, expected {self.leaf_shapes[v]}")
-        return ptrs
+            if tuple(t.shape) != self.leaf_shapes[v] and t.numel() != math.prod(self.leaf_shapes[v]):
+                raise ValueError(f"leaf {v} has shape {tuple(t.shape)}, expected {self.leaf_shapes[v]}")
+        return _dev_ptrs(leaves)
 
     def workspace(self, nbytes=None, stream=None):
         n = self.info()["workspace_bytes"] if nbytes is None else int(nbytes)
@@ -350,8 +370,9 @@ class Plan:
 
 class Batch:
     """Many unsliced plans of one precision contracted by one graph launch
-    (tn_batch): tiny contractions in an interpreter kernel (one workgroup per
-    network), large ones with the ordinary kernels."""
+    (tn_batch): the groups of small contractions in one launch, the rest level
+    by level, medium contractions of all networks together and large ones with
+    the ordinary kernels."""
 
     def __init__(self, plans):
         self.plans = list(plans)   # kept for shapes and dtypes only

@@ -9,6 +9,7 @@ instructions are disabled for the device code (see the hipcc flags).
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
 
@@ -26,14 +27,17 @@ FLAGS = [
 
 
 def build_leaves(verbose: bool = False) -> str:
-    """The binding's host extension (csrc/leaves.cpp), compiled against the
-    installed PyTorch's headers."""
+    """The binding's host extension (csrc/leaves.cpp), compiled for the host
+    against the installed PyTorch's headers."""
     import sysconfig
 
     import torch
     from torch.utils import cpp_extension
     out = os.path.join(HERE, "_leaves.so")
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+    # any host compiler: the one that ROCm ships where there is no other (not
+    # hipcc, which would link a second HIP runtime beside PyTorch's own)
+    cxx = os.environ.get("CXX") or shutil.which("g++") or os.path.join(os.path.dirname(HIPCC), "amdclang++")
+    cmd = [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"]
     for d in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
         cmd += ["-isystem", d]
