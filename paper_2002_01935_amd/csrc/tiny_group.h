@@ -155,7 +155,8 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
   // other op in between (`stage` counts the alternations, so no path leaves a
   // group and returns to it).  A group that exceeds the limits is cut: a
   // contraction with too many others below it (forward) or the readers of one
-  // with too many above it (reverse) start groups of the next stage.
+  // with too many above it (reverse) start groups of the next stage.  A pass
+  // cuts every group at all places, so that a few passes do for any length.
   std::vector<char> cut(nops, 0);
   for (;;) {
     for (int i = 0; i < nops; i++) rep[i] = i;
@@ -239,23 +240,36 @@ static Prog group_small(const tn_plan_s* p, Prog& prog, int root_buf) {
           table + loads + 64 <= kTinyBlobLarge && table + 64 + peak * p->elem_bytes <= kTinyGroupLds)
         continue;
       fits = false;
+      // cut into parts of at most `limit` contractions (half, where LDS or the
+      // tables are the limit): counting from the inputs, then from the readers
+      const int size = (int)members[g].size(), limit = size > kTinyGroupOps ? kTinyGroupOps : std::max(1, size / 2);
       bool done = false;
       for (int i : members[g]) {
         below[i] = 1;
-        int most = 0;
-        inputs(i, [&](int q) { if (q >= 0 && small[q] && item[q].group == (int)g) { below[i] += below[q]; most = std::max(most, below[q]); } });
-        if (below[i] > kTinyGroupOps && most <= kTinyGroupOps && !cut[i]) { cut[i] = 1; done = true; }
+        inputs(i, [&](int q) { if (q >= 0 && small[q] && item[q].group == (int)g) below[i] = std::min(below[i] + below[q], size + 1); });
+        if (below[i] > limit && !cut[i]) {
+          cut[i] = 1;
+          below[i] = 1;
+          done = true;
+        }
       }
-      for (auto r = members[g].rbegin(); !done && r != members[g].rend(); ++r) {
-        const int i = *r;
-        above[i] = 1;
-        for (int q : readers[item[i].c]) if (small[q] && item[q].group == (int)g) above[i] += above[q];
-        if (above[i] <= kTinyGroupOps) continue;
-        for (int q : readers[item[i].c]) 
-          if (small[q] && item[q].group == (int)g && above[q] <= kTinyGroupOps && !cut[q]) { cut[q] = 1; done = true; }
+      if (!done)
+        for (auto r = members[g].rbegin(); r != members[g].rend(); ++r) {
+          const int i = *r;
+          above[i] = 1;
+          for (int q : readers[item[i].c])
+            if (small[q] && item[q].group == (int)g && !cut[q]) above[i] = std::min(above[i] + above[q], size + 1);
+          if (above[i] <= limit) continue;
+          for (int q : readers[item[i].c])
+            if (small[q] && item[q].group == (int)g && !cut[q]) { cut[q] = 1; done = true; }
+          above[i] = 1;
+        }
+      if (!done) {
+        std::vector<int> open;
+        for (int i : members[g])
+          if (!cut[i]) open.push_back(i);
+        for (size_t i = open.size() / 2; i < open.size(); i++) { cut[open[i]] = 1; done = true; }
       }
-      for (auto r = members[g].rbegin(); !done && r != members[g].rend(); ++r)
-        if (!cut[*r]) { cut[*r] = 1; done = true; }
       if (!done) {                                       // cannot be cut: its last contraction is launched by itself
         const int i = members[g].back();
         small[i] = 0;

@@ -117,6 +117,34 @@ def test_random_program_sliced(emu, oracle_lib, tmp_path):
     check(emu, oracle_lib, tmp_path, net, tree, list(range(net.n_leaves)), sliced=sliced, ids=(0, 3, 5))
 
 
+def chain(length, dim):
+    """A vector times `length` - 1 matrices of dim x dim, one after another."""
+    idx = [[0]] + [[v - 1, v] for v in range(1, length)]
+    left = [0] + [length + v for v in range(length - 2)]
+    return idx, [dim] * length, [length - 1], Tree(np.array(left, np.int32), np.array(range(1, length), np.int32))
+
+
+@pytest.mark.parametrize("length,dim", [(400, 2), (700, 4), (40, 32)])
+def test_chains_cut_into_groups(emu, oracle_lib, tmp_path, length, dim):
+    """Connected sets of more contractions than one group takes, or than LDS holds."""
+    idx, dims, out, tree = chain(length, dim)
+    rng = np.random.default_rng(length)
+    leaves = [(rng.normal(size=(dim,) * len(t)) + 1j * rng.normal(size=(dim,) * len(t))) / (1.4 * dim ** 0.5) for t in idx]
+    check(emu, oracle_lib, tmp_path, Network(leaves, idx, dims, out), tree, list(range(0, length, 7)))
+
+
+def test_planning_time_of_long_chains():
+    """16,000 contractions in one connected set: planned in seconds, forward and
+    reverse (0.3 + 1 s; cutting one group per pass took 5 + 13 s)."""
+    import time
+
+    from paper_2002_01935_amd.binding import Plan
+    idx, dims, out, tree = chain(16000, 4)
+    t0 = time.perf_counter()
+    Plan(Network([None] * len(idx), idx, dims, out), tree).backward_info(list(range(0, 16000, 5)))
+    assert time.perf_counter() - t0 < 6
+
+
 def row_ops(emu, tmp_path, net, tree, sliced, wrt, prec, inflight):
     """(reverse, log2 rows, in-thread outputs, summed values, chunks or -1) of every row and split-K contraction."""
     describe(str(tmp_path), net, tree, sliced, (0,), wrt, [PREC[prec], 0, 0, inflight])
