@@ -308,15 +308,54 @@ static bool as_level(const Op& op, int prec, LevelOp& t) {
 struct ArenaUse {
   std::vector<std::pair<int64_t, int64_t>> reads, writes;   // [begin, end)
   bool known = true;
-  bool conflicts(const ArenaUse& later) const {
-    if (!known || !later.known) return true;
-    auto meet = [](const std::vector<std::pair<int64_t, int64_t>>& x, const std::vector<std::pair<int64_t, int64_t>>& y) {
-      for (auto& a : x)
-        for (auto& b : y)
-          if (a.first < b.second && b.first < a.second) return true;
-      return false;
-    };
-    return meet(writes, later.reads) || meet(writes, later.writes) || meet(reads, later.writes);
+};
+
+// Levels of a network's ops: the level of the last op that wrote, and of those
+// that read since, for every stretch of the arena.  An op goes one level above
+// all earlier ones that write what it touches or read what it writes.
+class ArenaLevels {
+ public:
+  int place(const ArenaUse& use) {
+    int level = floor_;
+    if (!use.known) {
+      level = floor_ = top_ + 1;                            // after all before it, before all behind it
+      top_ = floor_++;
+      return level;
+    }
+    for (auto& r : use.reads) each(r, [&](Part& p) { level = std::max(level, p.written + 1); });
+    for (auto& w : use.writes) each(w, [&](Part& p) { level = std::max(level, std::max(p.written, p.read) + 1); });
+    for (auto& r : use.reads) each(r, [&](Part& p) { p.read = std::max(p.read, level); });
+    for (auto& w : use.writes) each(w, [&](Part& p) { p.written = level; p.read = -1; });
+    top_ = std::max(top_, level);
+    return level;
+  }
+
+ private:
+  struct Part { int64_t end; int written, read; };
+  std::map<int64_t, Part> parts_;                           // by begin, disjoint
+  int floor_ = 0, top_ = -1;
+  void split(int64_t at) {
+    auto it = parts_.upper_bound(at);
+    if (it == parts_.begin()) return;
+    --it;
+    if (it->first == at || it->second.end <= at) return;
+    const Part rest = it->second;
+    it->second.end = at;
+    parts_[at] = rest;
+  }
+  template <typename F>
+  void each(const std::pair<int64_t, int64_t>& range, F&& f) {
+    split(range.first);
+    split(range.second);
+    auto it = parts_.lower_bound(range.first);
+    for (int64_t at = range.first; at < range.second; ++it) {
+      if (it == parts_.end() || it->first > at) {
+        const int64_t end = it == parts_.end() ? range.second : std::min(range.second, it->first);
+        it = parts_.insert(it, {at, Part{end, -1, -1}});
+      }
+      f(it->second);
+      at = it->second.end;
+    }
   }
 };
 
@@ -440,7 +479,7 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
     std::lock_guard<std::mutex> lk(p->mu);
     const std::vector<Op> prog = forward_program(p, 0);
     bool leading = true;
-    std::vector<std::pair<ArenaUse, int>> done;             // earlier ops and their levels
+    ArenaLevels levels;
     auto at_level = [&](int l) {
       if ((int)medium.size() <= l) {
         medium.resize((size_t)l + 1);
@@ -469,9 +508,7 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
         use.reads.insert(use.reads.end(), r.reads.begin(), r.reads.end());
         use.writes.insert(use.writes.end(), r.writes.begin(), r.writes.end());
       }
-      int level = 0;
-      for (auto& d : done)
-        if (d.first.conflicts(use)) level = std::max(level, d.second + 1);
+      const int level = levels.place(use);
       at_level(level);
       LevelOp t;
       if (as_level(op, prec, t)) {
@@ -482,7 +519,6 @@ extern "C" int tn_batch(int32_t n_plans, const tn_plan_t* plans, tn_batch_t* bat
         b->big[(size_t)level][(size_t)j].push_back(op);
         if (reduced) b->big[(size_t)level][(size_t)j].push_back(prog[i + 1]);
       }
-      done.push_back({use, level});
       if (reduced) i++;
     }
     b->n_leaves.push_back(p->n_leaves);
