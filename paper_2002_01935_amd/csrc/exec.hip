@@ -122,7 +122,8 @@ extern "C" int tn_plan(int32_t n_leaves, const int32_t* rank, const int64_t* lea
     return set_err(rc, err);
   }
   // splitting complex128 GEMMs must not push a plan out of the static scratch
-  if (p->prec == TN_C128 && p->workspace_bytes > kStaticScratchBytes && p->workspace_bytes <= 4 * kStaticScratchBytes) {
+  const bool splits = std::any_of(p->fwd.begin(), p->fwd.end(), [](const Op& o) { return o.kind == OpKind::Gemm && o.gemm.k_inner_bits > 0; });
+  if (splits && p->workspace_bytes > kStaticScratchBytes && p->workspace_bytes <= 4 * kStaticScratchBytes) {
     tn_plan_s* q = new tn_plan_s();
     q->n_leaves = p->n_leaves; q->n_idx = p->n_idx; q->n_out = p->n_out; q->n_sliced = p->n_sliced;
     q->rank = p->rank; q->leaf_idx = p->leaf_idx; q->idx_dim = p->idx_dim; q->out_idx = p->out_idx; q->sliced = p->sliced;
