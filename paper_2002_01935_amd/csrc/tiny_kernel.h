@@ -45,22 +45,26 @@ __device__ __forceinline__ void tiny_group(const Ctx& ctx, uint64_t blob, int g,
   V* data = reinterpret_cast<V*>(smem + 16 * d.tab_units);
   for (uint32_t i = tid; i < d.tab_units; i += nt)
     reinterpret_cast<u4*>(smem)[i] = reinterpret_cast<GMEM const u4*>(blob + d.tab_off)[i];
-  // external operands, 16 threads each: all loads of the group in flight together
+  // external operands, 16 threads each, or more where they are few (three of 2^10
+  // values 65 us with 16, 12 with 128): all loads of the group in flight together
   GMEM const uint64_t* ptrs = reinterpret_cast<GMEM const uint64_t*>(ctx.ws + ctx.ptrtab_off);
-  for (uint32_t i = tid >> 4; i < d.n_loads; i += nt >> 4) {
+  uint32_t lanes = 16;
+  while (2 * lanes <= nt && 2 * lanes * d.n_loads <= nt) lanes *= 2;
+  const uint32_t first = tid & (lanes - 1);
+  for (uint32_t i = tid / lanes; i < d.n_loads; i += nt / lanes) {
     const uint64_t w = reinterpret_cast<GMEM const uint64_t*>(blob + d.ld_off)[i];
     const uint32_t src = (uint32_t)w, lds = (uint32_t)(w >> 32) & 0xFFFFu;
     const uint32_t kind = (uint32_t)(w >> 48) & 0xFFu, n_bits = (uint32_t)(w >> 56);
     if (kind != 2) {
       const uint64_t base = kind == 0 ? ptrs[src] : ctx.ws + ctx.arena_off + uint64_t(z) * ctx.arena_stride + 256 * uint64_t(src);
-      for (uint32_t e = tid & 15; e < (1u << n_bits); e += 16) data[lds + e] = ld(reinterpret_cast<GMEM const V*>(base) + e);
+      for (uint32_t e = first; e < (1u << n_bits); e += lanes) data[lds + e] = ld(reinterpret_cast<GMEM const V*>(base) + e);
     } else {
       GMEM const TinyExt* x = reinterpret_cast<GMEM const TinyExt*>(blob + d.ext_off) + src;
       uint64_t off = 0;
       const int ns = x->ref.n_slice;
       for (int j = 0; j < ns; j++) off |= uint64_t((sid >> x->ref.slice_bit[j]) & 1) << x->ref.slice_pos[j];
       GMEM const V* S = reinterpret_cast<GMEM const V*>(ptrs[x->ref.slot]) + off;
-      for (uint32_t e = tid & 15; e < (1u << n_bits); e += 16) {
+      for (uint32_t e = first; e < (1u << n_bits); e += lanes) {
         uint32_t o = 0;
         for (uint32_t j = 0; j < n_bits; j++) o |= ((e >> j) & 1u) << x->pos[j];
         data[lds + e] = ld(S + o);
