@@ -520,12 +520,14 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     // complex64 results are gradients; complex64 forward values keep the sums
     // they had): 64 x 64 tiles fill the chip with 2^9 blocks, each summing at
     // least 2^6 values (about 7 us of FP64 matrix-core work, 3.5 us in FP32);
-    // the partial buffer stays at most as large as the larger operand.  In
-    // complex128 the sum has that order also where the workspace has no room
-    // for the partial tiles (split_f64 off), so that a value does not depend
-    // on the number of slices in flight.
+    // the partial buffer stays at most as large as the larger operand.  A value
+    // must not depend on the number of slices in flight, which fill the chip
+    // themselves: the reverse program of a sliced complex64 plan is not split
+    // further (3M, 32 slices of 2^2 x 2^6 x 2^8 x 2^9 640 us, split 890), and in
+    // complex128 the sum has the order of the splits also where there are none
+    // (enough slices, or no room for the partial tiles: split_f64 off).
     ks = std::max(ks, 0);
-    if (p->prec == TN_C128 || p->reverse) {
+    if (p->prec == TN_C128 || (p->reverse && p->d_sliced == 1)) {
       const int tiles64 = std::max(0, fa - 6) + std::max(0, fb - 6) + h;
       const int more = std::min(std::min(k - 6, 9 - tiles64), std::max(h + fa + k, h + fb + k) - (h + fa + fb));
       const int inner = std::max(0, std::min(more, 10) - ks);

@@ -1,4 +1,5 @@
-"""Launch rules of the complex128 GEMMs, decided on the host."""
+"""Launch rules of GEMMs, decided on the host: tiles and splits of complex128
+ones, splits of the reverse program."""
 
 import numpy as np
 import pytest
@@ -49,3 +50,16 @@ def test_partial_tiles_stay_within_the_static_scratch(shape):
         plain = nb * 16 * (2 ** (m + n) + (2 ** (m + n + hi) if hi else 0))
         if plain + 8192 <= 64 << 20:
             assert plan.info()["workspace_bytes"] <= 64 << 20, nb
+
+
+@pytest.mark.parametrize("prec", ["c64_4m", "c64_3m", "c64_bf16x3"])
+def test_reverse_gemms_of_sliced_plans_are_not_split_for_parallelism(prec):
+    """Slices in flight fill the chip; an unsliced plan splits its reverse GEMMs
+    (the workspace holds their partial tiles), a sliced one does not."""
+    from paper_2002_01935_amd.binding import Plan
+    net, _ = node(7, 12, 7)
+    split = Plan(net, TWO, precision=prec).backward_info([0, 1])["workspace_bytes"]
+    net, S = node(7, 12, 7, 2)
+    for nb in (1, 4):
+        plan = Plan(net, TWO, sliced=S, precision=prec, max_inflight_slices=nb)
+        assert plan.backward_info([0, 1])["workspace_bytes"] < nb * split
