@@ -45,8 +45,8 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 PEAK = {"c64_4m": 157.3, "c64_3m": 157.3, "c64_bf16x3": 2500.0, "c128": 78.6}
-# real FLOPs the matrix cores execute per 8C FLOPs of the tree: 4M and the
-# vector-ALU complex128 path 1; 3M three real products (6C); BF16x3 three
+# real FLOPs the matrix cores execute per 8C FLOPs of the tree: 4M and
+# complex128 (the same embedding in FP64) 1; 3M three real products (6C); BF16x3 three
 # BF16 products of the 4M embedding (24C)
 EXECUTED = {"c64_4m": 1.0, "c64_3m": 0.75, "c64_bf16x3": 3.0, "c128": 1.0}
 KERNEL = {"c64_4m": "gemm_mfma_4m", "c64_3m": "gemm_mfma_3m", "c64_bf16x3": "gemm_mfma_bf16x3", "c128": "gemm_mfma_f64"}
@@ -463,8 +463,8 @@ def qaoa_bench(n, p, n_streams):
     light-cone network per edge, each with its own tree and plan (complex64
     4M), contracted back to back on one stream, round-robin over `n_streams`
     streams (default priority, one workspace per plan), and all terms in one
-    graph launch (tn_batch: tiny contractions in the interpreter kernel, one
-    workgroup per term); plan by plan the many small networks are
+    graph launch (tn_batch: groups of small contractions, then levels of the
+    rest over all terms); plan by plan the many small networks are
     launch-latency bound."""
     import numpy as np
     import torch
@@ -528,7 +528,7 @@ def qaoa_bench(n, p, n_streams):
                       "terms": len(plans), "leaves_per_term_max": max(len(l) for l in leaves),
                       "flops_8C_total": flops, "plan_s": round(t_plan, 2), **res,
                       "batch": {"prepare_s": round(t_prep, 3), "launches_per_call": binfo["launches"],
-                                "interpreter_levels": binfo["levels"], "interpreted_contractions": binfo["tiny_ops"],
+                                "levels": binfo["levels"], "contractions_in_shared_launches": binfo["tiny_ops"],
                                 "workspace_MiB": round(binfo["workspace_bytes"] / 2 ** 20, 1),
                                 "launches_per_term_unbatched": round(sum(len(pl.nodes()) for pl in plans) / len(plans), 1)},
                       "tflops_best": round(flops / min(res.values()) / 1e12, 4), "energy": energy,

@@ -170,10 +170,12 @@ int tn_plan_node_info(tn_plan_t plan, int32_t k, int32_t* kernel_class, int32_t*
  * layout class); the default variant stays unless another is faster by more
  * than 1 %, so that repeated runs execute the same kernels.  Without it, a
  * contraction takes the default: the direct-to-LDS variant where its
- * operands allow (tile 9 for TN_C64_4M, 7 for TN_C64_3M, 11 on pre-split
- * BF16x3 operands), else tile 0 (10 on pre-split operands).  Clears a tile
- * pinned by tn_plan_set_tile.  Overwrites the workspace; synchronises the
- * stream.
+ * operands allow (tile 7 for TN_C64_3M, 11 on pre-split BF16x3 operands; for
+ * TN_C64_4M tile 15 below 256 blocks of 128x128, slices in flight and splits
+ * included, 14 from there on, and for less than 2^9 summed values per block
+ * 15 below 512 blocks and 9 from there on), else tile 0 (10 on pre-split
+ * operands, 16 for TN_C64_4M below 512 blocks).  Clears a tile pinned by
+ * tn_plan_set_tile.  Overwrites the workspace; synchronises the stream.
  */
 int tn_plan_tune(tn_plan_t plan, void* workspace, uint64_t workspace_bytes, void* stream);
 
@@ -181,7 +183,8 @@ int tn_plan_tune(tn_plan_t plan, void* workspace, uint64_t workspace_bytes, void
  * Pin the tile variant of every matrix-core contraction of the plan (forward
  * and backward programs, also one built later) that variant `tile` can run,
  * in place of the default or autotuned choice; the others keep theirs.  Variants: 0 = 128x128,
- * 1 = 64x128, 2 = 128x64, 3 = 64x64 (every precision); 4 = vector ALU; for
+ * 1 = 64x128, 2 = 128x64, 3 = 64x64 (every complex64 mode); 4 = vector ALU
+ * (for TN_C128, its only variant: the FP64 matrix cores); for
  * TN_C64_4M also 5 = 256x128 and 6 = 128x128 with raised matrix-core
  * priority; for TN_C64_4M and TN_C64_3M 7 = 128x128, 8 = 256x128 and
  * 9 = 128x128 at more waves per SIMD, all direct-to-LDS (operands whose
@@ -266,7 +269,7 @@ int tn_contract_sliced_timed(tn_plan_t plan, const void* const* leaves, int64_t 
 /*
  * Kernel of internal node k's contraction in the forward program, for
  * reporting: *tile receives the matrix-core tile variant (-1 for vector-ALU
- * kernels; 4 for complex128 products), `name` (capacity name_cap bytes, NUL
+ * kernels; 4 for complex128 products on the FP64 matrix cores), `name` (capacity name_cap bytes, NUL
  * terminated, truncated if short) the kernel's name with its template
  * arguments, e.g. "gemm_mfma_4m_dl<128,128,2,2,3>".  Either may be NULL.
  * TN_E_INVALID for k outside [0, number of internal nodes).  Host-only.

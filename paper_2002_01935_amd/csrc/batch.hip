@@ -163,8 +163,8 @@ __device__ __forceinline__ typename C2<T>::t thread_sum(GMEM const typename C2<T
 
 // A level's medium contractions of all networks.  Latency bound (a few
 // microseconds of dependent loads); a launch per contraction would pay that
-// and the launch each time.  81 QAOA terms: 12 levels, 60 launches per call in
-// place of 624, 4.56 -> 1.89 ms against one workgroup per network running up
+// and the launch each time.  81 QAOA terms: 12 levels, 62 launches per call in
+// place of 624, 4.56 -> 1.59 ms against one workgroup per network running up
 // to 2^16 multiply-adds per contraction (410 us per launch) between launches.
 template <typename T>
 __global__ __launch_bounds__(kLevelThreads) void level_kernel(CMEM const Ctx* ctxs, CMEM const LevelOp* ops,

@@ -421,7 +421,10 @@ static int64_t split_chain(int k, int ks) {
 // with other axis orders, cotangents) the lanes take the three lowest of A and
 // fill up with the lowest of B, so that both are read in runs of 64 bytes
 // instead of A in one run and B an element per cache line; the steps go on with
-// the next of either.  Returns whether the order changed.
+// the next of either.  Measured against A's order for 2^1 to 2^13 rows: A in one
+// run and B reversed 1.0 to 3.4 times as fast (2^1 x 2^1 x 2^22 218 -> 64 us, 2^10
+// x 2^2 x 2^14 204 -> 146), both shuffled 0.96 to 2.2 (2^6 x 2^3 x 2^16 102 -> 86, 2^4
+// x 2^2 x 2^18 66 -> 68).  Returns whether the order changed.
 static bool order_split_sum(std::vector<int>& K, const Layout& A, const Layout& B) {
   std::vector<int> byB = K;
   std::sort(byB.begin(), byB.end(), [&](int x, int y) { return B.pos_of(x) < B.pos_of(y); });
@@ -573,8 +576,9 @@ static Op make_contract(const tn_plan_s* p, const Operand& A0, const Operand& B0
     const int ks_most = splitk ? std::min(k - 6, std::max(0, 15 - rows_most)) : 0;
     int ks = splitk && p->reverse ? std::min(k - 6, std::max(0, 12 - rows_most)) : ks_most;
     // summed bits in another order in B (the sum's order is then new anyway)
-    // and few rows, none of B's: one wavefront takes all rows, 2^10 or 2^11 of
-    // them (2^12: 166 us per call instead of 145 on 2^3 x 2^2 x 2^22), with up to 32 complex sums per lane in FP32, 16 in FP64
+    // and few rows, none of B's: one wavefront takes all rows, with up to 32
+    // complex sums per lane in FP32, 16 in FP64, and 2^10 or 2^11 of them (2^3 x
+    // 2^2 x 2^22: 145 us per call, 2^12 wavefronts 166)
     const bool scattered = splitk && order_split_sum(K, A.lay, B.lay);
     const bool narrow = scattered && h == 0 && fa >= 1 && fa <= 3 && fb <= 2 &&
                         fa + fb <= (p->elem_bytes == 8 ? 5 : 4) && k >= 17;
